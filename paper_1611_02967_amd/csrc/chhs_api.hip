@@ -26,6 +26,8 @@ using chhs::LevelDesc;
 using chhs::Range;
 using chhs::Step3Task;
 using chhs::StripTask;
+using chhs::TailDesc;
+using chhs::TailOwner;
 using chhs::TileTask;
 using chhs::kMaxLevels;
 
@@ -83,7 +85,18 @@ struct Layout {
     int seg[kMaxLevels] = {};               // rows per strip segment of S[l]
     // per level and instance: x / y extent of the grids in S[l] (-1: not listed)
     std::vector<std::vector<int>> snx, sny;
+    // the coarse tail of the hierarchy that the cycles run on (FP32 in mixed
+    // precision): instances with an owner thread per pair of cells (own: 0 or 1
+    // per instance), their workgroups' threads and LDS, the owner tables and
+    // level descriptions; the other instances and their LDS
+    std::vector<int> own;
+    int own_threads = 0;
+    size_t own_lds = 0;
+    std::vector<TailOwner> owners;
+    std::vector<TailDesc<double>> tails;
+    std::vector<TailDesc<float>> tails32;
     std::vector<int> tail_insts;
+    size_t tail_lds = 0;
     std::vector<CellTask> A0n;              // finest-level cells of instances without a fused norm
     std::vector<CellTask> A0t;              // finest-level cells of instances held by the tail
     std::vector<CellTask> A0x;              // 3D mixed: finest cells refined per cell
@@ -103,9 +116,9 @@ struct Layout {
     // kChainCells cells in every instance)
     int chain_from = 0;
     std::vector<int> max_cells;
-    size_t tail_lds = 0, tail_lds32 = 0;
     // offsets into the workspace
-    size_t off_desc = 0, off_desc32 = 0, off_info = 0, off_tail = 0, off_rngA0 = 0, off_rngT0 = 0,
+    size_t off_desc = 0, off_desc32 = 0, off_info = 0, off_tail = 0, off_owners = 0,
+           off_tails = 0, off_rngA0 = 0, off_rngT0 = 0,
            off_rngA0n = 0;
     size_t off_A0n = 0, off_A0t = 0, off_partial_t = 0, off_A0x = 0, off_rngA0x = 0;
     size_t off_M0 = 0, off_rngM0 = 0, off_rngM0f = 0, off_FM0 = 0;
@@ -147,6 +160,9 @@ struct chhs_ctx {
     Range* rngM0f = nullptr;
     Table<FoldTask> FA0, FA0n;
     int* tail_insts = nullptr;
+    TailOwner* owners = nullptr;
+    TailDesc<double>* tails = nullptr;
+    TailDesc<float>* tails32 = nullptr;
     Range* rngA0 = nullptr;
     Range* rngT0 = nullptr;
     Range* rngA0n = nullptr;
@@ -296,6 +312,103 @@ int pick_tail(const std::vector<int>& cells, bool mixed, size_t* bytes, size_t* 
     *bytes = chhs::tail_lds_bytes(&cells[nlev - 1], 1, sizeof(double), 11);
     *bytes32 = chhs::tail_lds_bytes(&cells[nlev - 1], 1, sizeof(float), 12);
     return nlev - 1;
+}
+
+// Owner threads of the tail from level top on (ext: three extents per level).
+int own_threads(const std::vector<int>& ext, int top) {
+    int t = 0;
+    for (int l = top; l < int(ext.size() / 3); ++l) {
+        const int np = chhs::own_pairs(ext[3 * l], ext[3 * l + 1], ext[3 * l + 2]);
+        t = chhs::own_place(t, np) + np;
+    }
+    return (t + 63) & ~63;
+}
+
+// The owner threads of one instance's tail (own: one entry per thread, all
+// zero on entry) and the description of its levels.  desc: the instance's
+// levels, their phi_* and phi^m in one workspace (close together: the tail's
+// levels are small and allocated one after another).
+template <typename T>
+void tail_owners(int dim, int top, int nlev, int order, const LevelDesc<T>* desc, TailOwner* own,
+                 TailDesc<T>& d) {
+    constexpr bool corr = std::is_same<T, float>::value;
+    const int K = 2 * dim - 1;
+    for (int k = 0; k < 3; ++k) {
+        d.u[k] = desc[top].u[0][k];
+        d.f[k] = top > 0 ? desc[top].fr[k] : desc[top].f[k];
+    }
+    d.b = desc[top].b;
+    d.pstar = desc[top].pstar;
+    d.psi = desc[top].psi;
+    d.lam = desc[top].lam;
+    d.kap = desc[top].kap;
+    d.gamma = desc[top].gamma;
+    d.levels = nlev - top;
+    d.finest = top == 0 ? 1 : 0;
+    d.cubic = order == 1 ? 1 : 0;
+    d.single = d.joined = 0;
+    int t = 0, off = 0, prev_wave = -1;
+    for (int l = top; l < nlev; ++l) {
+        const LevelDesc<T>& D = desc[l];
+        const int nx = D.nx, ny = D.ny, nz = D.nz, np = chhs::own_pairs(nx, ny, nz);
+        t = chhs::own_place(t, np);
+        if (np <= 64) {
+            d.single |= 1u << (l - top);
+            if (prev_wave == t / 64) d.joined |= 1u << (l - top - 1);
+            prev_wave = t / 64;
+        } else {
+            prev_wave = -1;
+        }
+        const int hx = (nx + 1) / 2;
+        for (int q = 0; q < np; ++q) {
+            // above the coarsest level the pairs of one coarse cell are
+            // 2^(dim - 1) consecutive threads
+            int m, j, k = 0;
+            bool lead = true;
+            if (l + 1 < nlev) {
+                const int c = q >> (dim - 1), crow = c / hx;
+                m = c % hx;
+                lead = (q & ((1 << (dim - 1)) - 1)) == 0;
+                if (dim == 3) {
+                    k = 2 * (crow / (ny / 2)) + ((q >> 1) & 1);
+                    j = 2 * (crow % (ny / 2)) + (q & 1);
+                } else {
+                    j = 2 * crow + (q & 1);
+                }
+            } else {
+                m = q % hx;
+                j = q / hx % ny;
+                k = q / hx / ny;
+            }
+            TailOwner& o = own[t + q];
+            const int i = 2 * m, red = (j + k) & 1;
+            o.cell0 = (k * ny + j) * nx + i;
+            o.par = ((k / 2) * (ny / 2) + j / 2) * (nx / 2) + m;
+            o.nx = nx;
+            o.nxy = nx * ny;
+            o.n = D.n;
+            o.off = off;
+            o.ps = int(D.pstar - d.pstar) + o.cell0;
+            o.psi = int(D.psi - d.psi) + o.cell0;
+            const bool both = i + 1 < nx;
+            o.fl = (1u << chhs::kOwnValid) | (both ? 1u << chhs::kOwnMid : 0u) |
+                   (red ? 1u << chhs::kOwnRed : 0u) | (lead ? 1u << chhs::kOwnFirst : 0u) |
+                   (unsigned(l - top) << chhs::kOwnLevel);
+            if (corr && dim == 2 && l + 1 == nlev && nx % 2 == 0 && D.n <= 128)
+                o.fl |= 1u << chhs::kOwnKapFirst;
+            for (int c = 0; c < 2; ++c) {
+                const int e = c ^ red;
+                if (e == 1 && !both) continue;
+                const bool has[5] = {e == 0 ? i > 0 : i + 2 < nx, j > 0, j + 1 < ny, k > 0,
+                                     k + 1 < nz};
+                o.fl |= 1u << c;
+                for (int f = 0; f < K; ++f)
+                    if (has[f]) o.fl |= 1u << (2 + c * K + f);
+            }
+        }
+        t += np;
+        off += chhs::own_words(D.n, corr);
+    }
 }
 
 void cell_tasks(std::vector<CellTask>& out, int inst, int n) {
@@ -540,8 +653,20 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         for (int l = 0; l < nlev; ++l) cells[l] = ext[3 * l] * ext[3 * l + 1] * ext[3 * l + 2];
         size_t tb = 0, tb32 = 0;
         const int tail = pick_tail(cells, mixed, &tb, &tb32);
-        L.tail_lds = std::max(L.tail_lds, tb);
-        L.tail_lds32 = std::max(L.tail_lds32, tb32);
+        // Tails whose pairs each get an owner thread take the owner-thread kernel
+        // (at 32^2 FP64 22 against 54 us a cycle); the others, of a top level of
+        // more than about 1150 cells (FP64 3D 900), keep the cells-by-stride one.
+        const int own = own_threads(ext, tail);
+        L.own.push_back(own <= chhs::own_max_threads(dim, mixed) ? 1 : 0);
+        if (L.own.back()) {
+            L.own_threads = std::max(L.own_threads, own);
+            size_t words = 0;
+            for (int l = tail; l < nlev; ++l) words += chhs::own_words(cells[l], mixed);
+            L.own_lds = std::max(L.own_lds, words * (mixed ? sizeof(float) : sizeof(double)));
+        } else {
+            L.tail_insts.push_back(i);
+            L.tail_lds = std::max(L.tail_lds, mixed ? tb32 : tb);
+        }
         InstInfo in{};
         in.dim = dim;
         in.nlev = nlev;
@@ -640,7 +765,21 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         if (!in.fused) cell_tasks(L.A0n, i, cells[0]);
         if (!in.fused && mixed && dim == 3 && step3d_opts(dim, o)) cell_tasks(L.A0x, i, cells[0]);
         if (tail == 0) cell_tasks(L.A0t, i, cells[0]);
-        L.tail_insts.push_back(i);
+    }
+    // the owner threads and levels of the tails
+    L.owners.assign(size_t(n_inst) * L.own_threads, TailOwner{});
+    L.tails.assign(mixed ? 0 : n_inst, TailDesc<double>{});
+    L.tails32.assign(mixed ? n_inst : 0, TailDesc<float>{});
+    for (int i = 0; base != nullptr && i < n_inst; ++i) {
+        if (!L.own[i]) continue;
+        TailOwner* own = &L.owners[size_t(i) * L.own_threads];
+        const InstInfo& in = L.info[i];
+        if (mixed)
+            tail_owners(dim, in.tail, in.nlev, in.order, &L.desc32[size_t(i) * kMaxLevels], own,
+                        L.tails32[i]);
+        else
+            tail_owners(dim, in.tail, in.nlev, in.order, &L.desc[size_t(i) * kMaxLevels], own,
+                        L.tails[i]);
     }
     // 2D smoother per level: row-streaming strips or square tiles (the same
     // choice for the FP64 and the FP32 hierarchy)
@@ -733,6 +872,8 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     L.off_desc32 = take(std::max<size_t>(1, L.desc32.size()) * sizeof(LevelDesc<float>));
     L.off_info = take(L.info.size() * sizeof(InstInfo));
     L.off_tail = take(L.tail_insts.size() * sizeof(int));
+    L.off_owners = take(L.owners.size() * sizeof(TailOwner));
+    L.off_tails = take(n_inst * sizeof(TailDesc<double>));
     L.off_rngA0 = take(n_inst * sizeof(Range));
     L.off_rngT0 = take(n_inst * sizeof(Range));
     L.off_rngA0n = take(n_inst * sizeof(Range));
@@ -890,17 +1031,16 @@ Batch<float> batch32(chhs_ctx* c, int level, const int* active) {
 }
 
 // The hierarchy of one precision: device descriptors, host copies, current
-// copies of u per level, tail LDS bytes.
+// copies of u per level.
 template <typename T>
 struct Hier {
     const LevelDesc<T>* dev;
     const std::vector<LevelDesc<T>>* host;
     int* cur;
-    size_t tail_lds;
 };
 
-Hier<double> hier64(chhs_ctx* c) { return {c->ddesc, &c->lay.desc, c->cur, c->lay.tail_lds}; }
-Hier<float> hier32(chhs_ctx* c) { return {c->ddesc32, &c->lay.desc32, c->cur32, c->lay.tail_lds32}; }
+Hier<double> hier64(chhs_ctx* c) { return {c->ddesc, &c->lay.desc, c->cur}; }
+Hier<float> hier32(chhs_ctx* c) { return {c->ddesc32, &c->lay.desc32, c->cur32}; }
 
 // One 2D smoothing launch on level l (row-streaming strips or tiles, as
 // planned; all = every instance, else those whose tail starts below l);
@@ -1067,10 +1207,18 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true) {
         // an instance's tail level is only ever written by the restriction into
         // it (copy 0) and by the tail itself: it is always read from copy 0
         TimedScope t(c, depth == 0 ? CHHS_K_PRE0 : CHHS_K_COARSE);
-        chhs::launch_tail<T, !kPlain>(dim, H.dev, c->dinfo, c->tail_insts, c->n_inst, act, 0u,
-                                      cycle_shape(o),
-                                      kPlain && c->defer_shift ? c->res : nullptr, H.tail_lds,
-                                      c->stream);
+        const TailDesc<T>* tails;
+        if constexpr (kPlain)
+            tails = c->tails;
+        else
+            tails = c->tails32;
+        double* pend = kPlain && c->defer_shift ? c->res : nullptr;
+        if (c->lay.own_threads > 0)
+            chhs::launch_tail_own<T, !kPlain>(dim, tails, c->owners, c->n_inst, act, cycle_shape(o),
+                                              pend, c->lay.own_threads, c->lay.own_lds, c->stream);
+        chhs::launch_tail<T, !kPlain>(dim, H.dev, c->dinfo, c->tail_insts,
+                                      int(c->lay.tail_insts.size()), act, 0u, cycle_shape(o), pend,
+                                      c->lay.tail_lds, c->stream);
     }
     const bool bil = o.prolong == 1;
     for (int d = depth - 1; d >= 0; --d) {
@@ -2003,13 +2151,21 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
         delete c;
         return code;
     };
-    if (chhs::prepare_tail<double, false>(c->dim, L.tail_lds) != 0) return fail(CHHS_E_HIP);
-    if (c->mixed && chhs::prepare_tail<float, true>(c->dim, L.tail_lds32) != 0)
+    if (L.own_threads > 0 &&
+        (c->mixed ? chhs::prepare_tail_own<float, true>(c->dim, L.own_threads, L.own_lds)
+                  : chhs::prepare_tail_own<double, false>(c->dim, L.own_threads, L.own_lds)) != 0)
+        return fail(CHHS_E_HIP);
+    if (!L.tail_insts.empty() &&
+        (c->mixed ? chhs::prepare_tail<float, true>(c->dim, L.tail_lds)
+                  : chhs::prepare_tail<double, false>(c->dim, L.tail_lds)) != 0)
         return fail(CHHS_E_HIP);
     c->ddesc = reinterpret_cast<LevelDesc<double>*>(b + L.off_desc);
     c->ddesc32 = reinterpret_cast<LevelDesc<float>*>(b + L.off_desc32);
     c->dinfo = reinterpret_cast<InstInfo*>(b + L.off_info);
     c->tail_insts = reinterpret_cast<int*>(b + L.off_tail);
+    c->owners = reinterpret_cast<TailOwner*>(b + L.off_owners);
+    c->tails = reinterpret_cast<TailDesc<double>*>(b + L.off_tails);
+    c->tails32 = reinterpret_cast<TailDesc<float>*>(b + L.off_tails);
     c->rngA0 = reinterpret_cast<Range*>(b + L.off_rngA0);
     c->rngT0 = reinterpret_cast<Range*>(b + L.off_rngT0);
     c->rngA0n = reinterpret_cast<Range*>(b + L.off_rngA0n);
@@ -2035,6 +2191,13 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
         hipMemcpyAsync(c->dinfo, L.info.data(), L.info.size() * sizeof(InstInfo),
                        hipMemcpyHostToDevice, st) != hipSuccess ||
         hipMemcpyAsync(c->tail_insts, L.tail_insts.data(), L.tail_insts.size() * sizeof(int),
+                       hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipMemcpyAsync(c->owners, L.owners.data(), L.owners.size() * sizeof(TailOwner),
+                       hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipMemcpyAsync(c->tails,
+                       c->mixed ? static_cast<const void*>(L.tails32.data())
+                                : static_cast<const void*>(L.tails.data()),
+                       n_inst * (c->mixed ? sizeof(TailDesc<float>) : sizeof(TailDesc<double>)),
                        hipMemcpyHostToDevice, st) != hipSuccess ||
         hipMemcpyAsync(c->rngA0, L.rngA0.data(), n_inst * sizeof(Range), hipMemcpyHostToDevice,
                        st) != hipSuccess ||

@@ -164,7 +164,8 @@ __device__ __forceinline__ float recip_ge1(float x) {
 // the parent and 1/4 of the parent's neighbour towards the cell, the parent
 // itself standing in beyond the boundary (even continuation, as the Neumann
 // ghost cells continue a field), applied axis by axis in the order z, y, x.
-template <int DIM, typename T>
+// S: stride of the values of one field (records of several fields).
+template <int DIM, typename T, int S = 1>
 __device__ __forceinline__ T bilinear_corr(const T* cv, const T* cb, int cnx, int cny, int cnz,
                                            int i, int j, int k) {
     const int pi = i >> 1, pj = j >> 1, pk = k >> 1;
@@ -173,7 +174,7 @@ __device__ __forceinline__ T bilinear_corr(const T* cv, const T* cb, int cnx, in
     const int nj = sj < 0 ? 0 : (sj >= cny ? cny - 1 : sj);
     const int nk = sk < 0 ? 0 : (sk >= cnz ? cnz - 1 : sk);
     auto d = [&](int kk, int jj, int ii) {
-        const int c = (kk * cny + jj) * cnx + ii;
+        const int c = S * ((kk * cny + jj) * cnx + ii);
         return cv[c] - cb[c];
     };
     if (DIM == 2) {

@@ -345,4 +345,65 @@ void launch_tail(int dim, const LevelDesc<T>* desc, const InstInfo* info, const 
                  int ninst, const int* active, unsigned cur_mask, const CycleShape& shape,
                  double* pend, size_t lds_bytes, hipStream_t st);
 
+// ---- the same with an owner thread per pair of cells (chhs_tail_own.hip) -----------
+// LDS of one tail level, in values: the records of u and one of zeros, the
+// restricted iterate, the restricted residual, phi_* and (correction form) b.
+__host__ __device__ constexpr int own_words(int n, bool corr) { return (corr ? 11 : 10) * n + 3; }
+// Threads at most (the kernel's registers per lane, without spilling).
+constexpr int own_max_threads(int dim, bool corr) {
+    return dim == 2 ? (corr ? 1024 : 768) : (corr ? 768 : 512);
+}
+// Owner threads: every pair of x-adjacent cells of every tail level has one
+// (the last pair of an odd row holds one cell).  Levels are placed finest
+// first: a level of more than 64 pairs starts at a wave, smaller ones share
+// waves without crossing one.
+__host__ __device__ inline int own_pairs(int nx, int ny, int nz) { return ((nx + 1) / 2) * ny * nz; }
+__host__ __device__ inline int own_place(int t, int np) {
+    return np > 64 || (t & 63) + np > 64 ? (t + 63) & ~63 : t;
+}
+template <typename T, bool CORR>
+int prepare_tail_own(int dim, int threads, size_t lds_bytes);
+// An owner thread's pair (x even, x + 1): its left cell, the coarse cell above
+// it, extents of its level, the level's place in LDS (values), the element
+// offsets of the left cell's phi_* and phi^m from TailDesc::pstar / psi.
+// Bits of fl: c: member of color c exists; 2 + c K + k (K = 2 dim - 1): its
+// outer face k (other x face, y - 1, y + 1, z - 1, z + 1) is interior; then as
+// named below; three bits from kOwnLevel on: the level counted from the tail's
+// top one.
+constexpr int kOwnMid = 12;     // both members exist
+constexpr int kOwnRed = 13;     // the red member is the right one
+constexpr int kOwnFirst = 14;   // first pair of its coarse cell
+constexpr int kOwnValid = 15;   // the thread owns a pair
+constexpr int kOwnLevel = 16;
+// 2D correction form, an even coarsest grid of at most 128 cells: kap nF is
+// rounded before it is added to chi', as k_tail does there
+constexpr int kOwnKapFirst = 19;
+struct TailOwner {
+    unsigned fl;
+    int cell0, par, nx, nxy, n, off, ps, psi;
+    int pad[3];
+};
+// The tail's levels of one instance: top level's iterate, right-hand side (the
+// finest level's f, else the restricted residual), b, lam, kap; bit l of
+// single: level l (from the top one) has at most 64 pairs; of joined: it
+// shares its wave with level l + 1.
+template <typename T>
+struct TailDesc {
+    T* u[3];
+    const T* f[3];
+    const T* b;
+    const T* pstar;
+    const T* psi;
+    T lam, kap, gamma;
+    int levels, finest, cubic;     // levels 0: the instance is not worked here
+    unsigned single, joined;
+};
+// One workgroup per instance (threads: at least every instance's owner threads,
+// and the stride of owners): the V-cycle over levels info.tail ..
+// info.nlev - 1 of that instance, always on copy 0 of u.
+template <typename T, bool CORR>
+void launch_tail_own(int dim, const TailDesc<T>* tails, const TailOwner* owners, int ninst,
+                 const int* active, const CycleShape& shape, double* pend, int threads,
+                 size_t lds_bytes, hipStream_t st);
+
 }  // namespace chhs

@@ -1,0 +1,74 @@
+"""GPU tests of the one-workgroup coarse tail at the sizes where its layout
+changes: one wave, several waves, levels that share a wave, odd coarsest
+extents, the last sizes whose pairs of cells each get an owner thread and the
+first that do not.
+
+One V-cycle agrees with the oracle's iterate by iterate to 1e-11 (some hundred
+roundings of values of order one, amplified by at most 1 / (h^2 s) in p); a
+mixed-precision step agrees with the oracle's to 1e-8, as both solve to 1e-10.
+"""
+import numpy as np
+import pytest
+
+from oracle import fas, scheme
+from workloads import uniform_field
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(4, 4), (14, 10), (12, 6), (8, 16), (16, 16), (28, 20), (24, 48), (32, 40), (64, 80),
+          (4, 4, 4), (6, 10, 14), (8, 8, 12), (8, 12, 10), (16, 24, 20)]
+
+
+@pytest.fixture(scope="module")
+def chhs():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from paper_1611_02967_amd import chhs as binding
+    return binding
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def _inputs(shape, seed):
+    prev = uniform_field(shape, seed, amp=0.6)
+    cur = prev + uniform_field(shape, seed + 1, amp=0.1)
+    return prev, cur, uniform_field(shape, seed + 2, amp=0.3), uniform_field(shape, seed + 3, amp=0.01)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("variant", [dict(), dict(prolong=1), dict(order=1)],
+                         ids=["plain", "bilinear", "first-order"])
+def test_one_vcycle_matches_oracle(chhs, shape, variant):
+    prm = scheme.Params(eps=0.05, gamma=2.0, s=1e-3, h=1.0 / shape[-1],
+                        order=variant.get("order", 2))
+    prev, cur, mu0, p0 = _inputs(shape, 8100)
+    sv = chhs.Solver(chhs.make_problem(shape, prm.h, prm.eps, prm.gamma, prm.s),
+                     chhs.chhs_default_opts(**variant))
+    sv.setup_step(dev(prev), dev(cur), dev(mu0), dev(p0))
+    sv.fas_vcycle()
+    phi_star, f = scheme.step_rhs(prev, cur, prm)
+    levels = fas.build_levels(phi_star, cur.copy(), f, prm.h)
+    us = [None] * len(levels)
+    us[0] = u = [cur.copy(), mu0.copy(), p0 - p0.mean()]
+    fas.vcycle(levels, us, 0, prm,
+               fas.Opts(prolong="bilinear" if variant.get("prolong") else "constant"))
+    u[2] -= u[2].mean()
+    for name, want in zip(("phi", "mu", "p"), u):
+        got = sv.read_field(0, name).cpu().numpy()
+        assert np.max(np.abs(got - want)) <= 1e-11, name
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_mixed_step_matches_oracle(chhs, shape):
+    prm = scheme.Params(eps=0.05, gamma=2.0, s=1e-3, h=1.0 / shape[-1])
+    prev, cur, mu0, p0 = _inputs(shape, 8200)
+    sv = chhs.Solver(chhs.make_problem(shape, prm.h, prm.eps, prm.gamma, prm.s),
+                     chhs.chhs_default_opts(precision=1))
+    t = [dev(v) for v in (prev, cur, mu0, p0)]
+    sv.step(*t, 1)
+    ref = fas.solve_step(prev, cur, mu0, p0 - p0.mean(), prm, fas.Opts(tol=1e-10))
+    assert np.max(np.abs(t[1].cpu().numpy() - ref.phi)) <= 1e-8
+    assert np.max(np.abs(t[2].cpu().numpy() - ref.mu)) <= 1e-8
