@@ -80,8 +80,9 @@ typedef struct chhs_problem {
  * is a mask of classes, bit (class + 1) set for each class to time.  Each
  * event pair delays the next launch by a few microseconds.  smoother selects
  * the 2D smoothing kernels of the levels above the single-workgroup tail:
- * 0 = default (row-streaming strips on the finest level, square LDS tiles on
- * coarser ones), 1 = tiles everywhere, 2 = strips on every level (including
+ * 0 = default (LDS tiles; row-streaming strips on the finest level in mixed
+ * precision, or when an instance has at least 3 2^20 cells), 1 = tiles
+ * everywhere (64 x 16 on the finest level), 2 = strips on every level (including
  * the explicit smoothing calls on tail levels).  On 3D levels above the tail:
  * 0 = the fused z-marching step on levels whose z segments hold at least 16
  * planes, per-cell red-black kernels (one launch per color) on the others,
@@ -89,19 +90,20 @@ typedef struct chhs_problem {
  * (3D second-order scheme only).  All kernels perform the same red-black
  * updates (results agree to rounding).
  * tile_threads = 0 (default) gives tiled levels 1024-thread blocks when they
- * have at most 256 tiles and 256-thread blocks otherwise; 256, 512 or 1024
+ * have at most 256 tiles, otherwise 512-thread (FP64) or 256-thread ones; 256, 512 or 1024
  * fixes the block size of every tiled level (the same arithmetic per cell).
- * tile_rows = 0 (default) cuts coarse tiled levels into 64 x 8 tiles when they
- * have at most 128 tiles of 64 x 16 (over the batch) and into 64 x 16 tiles
- * otherwise; 16, 8 or 4 fixes the tile height of every coarse tiled level
- * (the finest level has 64 x 16 tiles); 32 (precision = 1 only) gives the
- * finest level of the FP32 hierarchy 64 x 32 tiles (fewer halo cells
- * recomputed per cell) and leaves the coarse levels at their default.
+ * tile_rows = 0 (default) cuts tiled levels into 64 x 8 tiles when they have at
+ * most 128 tiles of 64 x 16 (over the batch; FP64 ones of at most 64 into 64 x 4)
+ * and into 64 x 16 tiles otherwise (in mixed precision, or with smoother = 1,
+ * the finest level always); 16, 8 or 4 fixes the tile height of every coarse
+ * tiled level (the finest level then has 64 x 16 tiles); 32 (precision = 1
+ * only) gives the finest level of the FP32 hierarchy 64 x 32 tiles (fewer halo
+ * cells recomputed per cell) and leaves the coarse levels at their default.
  * autotune = 1 (smoother = 0, second-order scheme): chhs_init times, on the
  * problem at hand, each level's smoothing launches and keeps the fastest per
  * level (the choice then depends on the device; results agree to rounding).
- * 2D (nu1, nu2 >= 1): tiles of 256, 512 and 1024 threads (on coarse levels
- * each with 16, 8 and 4 rows; on the FP32 finest level also 64 x 32 tiles of
+ * 2D (nu1, nu2 >= 1): tiles of 256, 512 and 1024 threads (each with 16, 8 and
+ * 4 rows, but on the FP32 finest level with 16; there also 64 x 32 tiles of
  * 512 and 1024 threads; the pre- and post-smoothing launches of a tile
  * height each take their fastest block size) and strips of 1/4, 1/2, 1, 2
  * and 4 times the default segment height.  3D: the fused step or the

@@ -22,7 +22,8 @@ LIB = os.path.join(HERE, "libchhs.so")
 STAMP = LIB + ".sha256"
 ARCH = "gfx950"
 
-SOURCES = ["chhs_api.hip", "chhs_kernels.hip", "chhs_tile2d.hip", "chhs_stream2d.hip",
+SOURCES = ["chhs_tile2d_l0.hip", "chhs_tile2d_f32.hip", "chhs_tile2d.hip", "chhs_api.hip",
+           "chhs_kernels.hip", "chhs_stream2d.hip",
            "chhs_tail.hip", "chhs_tail_own.hip", "chhs_noalloc.hip", "chhs_refine2d.hip",
            "chhs_step3d.hip", "chhs_resid3d.hip"]
 

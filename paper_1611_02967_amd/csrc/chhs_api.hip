@@ -41,11 +41,25 @@ constexpr long long kMaxPackedCells = 2147483647LL;
 // Tiled launches of at most this many blocks (at most one per compute unit)
 // use 1024-thread blocks: their time is the latency of one block.
 constexpr int kWideTiles = 256;
+// Levels of at most this many 64 x 16 tiles (over the batch) get 64 x 8 tiles,
+// FP64 ones of at most kTinyTileLevel 64 x 4 tiles: still at most one block per
+// compute unit, and each block's chain is shorter (one step of a 128^2 FP64
+// grid 537 us with 64 x 16 tiles on the finest level, 492 with 64 x 4).
 constexpr long kSmallTileLevel = 128;
+constexpr long kTinyTileLevel = 64;
+// FP64: the finest level is smoothed by row-streaming strips when an instance
+// has at least this many cells, by tiles otherwise: a strip's rows pass one
+// after another, so short levels leave most of the device idle (one step,
+// strips against 512-thread tiles: 512^2 1178 / 924 us, 1024^2 1980 / 1729, 2048 x
+// 1024 2769 / 2420, 32 x 256^2 2222 / 1825, 2048^2 4128 / 4388).  By the instance
+// and not by the batch, so that an instance of a batch is smoothed as it is
+// alone.
+constexpr long kStripCells = 3L << 20;
 // Threads per tile block: the autotuned choice (256, 512 or 1024), else by
-// the number of tiles.
-int tile_block(int chosen, int ntiles) {
-    return chosen > 0 ? chosen : (ntiles <= kWideTiles ? 1024 : 256);
+// the number of tiles (FP64 launches of more tiles than compute units: 512, at
+// 1024^2 7% of a step faster than 256).
+int tile_block(int chosen, int ntiles, bool fp64) {
+    return chosen > 0 ? chosen : (ntiles <= kWideTiles ? 1024 : (fp64 ? 512 : 256));
 }
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -415,11 +429,16 @@ void cell_tasks(std::vector<CellTask>& out, int inst, int n) {
     for (int c = 0; c < n; c += chhs::kBlock) out.push_back({inst, c});
 }
 
-void tile_tasks(std::vector<TileTask>& out, int inst, int nx, int ny, int tile_y) {
+// Norm partials of a tiled finest level: one per 64 x 4 cells.
+int tile_partials(int nx, int ny) { return ((nx + chhs::kTileX - 1) / chhs::kTileX) * ((ny + 3) / 4); }
+
+// part: the instance's first norm partial (finest level).
+void tile_tasks(std::vector<TileTask>& out, int inst, int nx, int ny, int tile_y, int part) {
     const int tx = (nx + chhs::kTileX - 1) / chhs::kTileX;
     const int ty = (ny + tile_y - 1) / tile_y;
     for (int by = 0; by < ty; ++by)
-        for (int bx = 0; bx < tx; ++bx) out.push_back({inst, bx, by});
+        for (int bx = 0; bx < tx; ++bx)
+            out.push_back({inst, bx, by, part + by * (tile_y / 4) * tx + bx});
 }
 
 // Strip tasks of one level over the instances listed (extents nx, ny, -1 =
@@ -509,8 +528,16 @@ void task_ranges(std::vector<Range>& r, int n_inst, const std::vector<Task>& tas
 void fused_ranges(Layout& L, int n_inst) {
     if (L.strip[0])
         task_ranges(L.rngT0, n_inst, L.S[0]);
-    else if (!L.T[0].empty())
-        task_ranges(L.rngT0, n_inst, L.T[0]);
+    else if (!L.T[0].empty()) {
+        L.rngT0.assign(n_inst, Range{0, 0});
+        int at = 0;
+        for (int i = 0; i < n_inst; ++i)
+            if (L.snx[0][i] >= 0) {
+                const int n = tile_partials(L.snx[0][i], L.sny[0][i]);
+                L.rngT0[i] = Range{at, at + n};
+                at += n;
+            }
+    }
     else
         task_ranges(L.rngT0, n_inst, L.Z64[0]);     // 3D
 }
@@ -624,8 +651,8 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     };
     // tile height per 2D level: opts.tile_rows on coarse levels if given, else
     // 64 x 8 on coarse levels with at most kSmallTileLevel 64 x 16 tiles over
-    // the batch (more, smaller blocks, each a shorter launch), 64 x 16
-    // elsewhere; the autotuner may cut coarse levels anew
+    // the batch (FP64: also on the finest level, and 64 x 4 with at most
+    // kTinyTileLevel), 64 x 16 elsewhere; the autotuner may cut a level anew
     for (int l = 0; l < kMaxLevels; ++l) L.tile_y[l] = chhs::kTileY;
     if (dim == 2) {
         std::vector<long> tiles16(kMaxLevels, 0);
@@ -638,12 +665,16 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         }
         const bool tall = o->tile_rows == chhs::kTileYTall;    // finest level only
         if (tall) L.tile_y[0] = chhs::kTileYTall;
-        for (int l = 1; l < kMaxLevels; ++l)
+        // an explicit smoother keeps 64 x 16 tiles on the finest level
+        const bool fp64 = !mixed && o->order != 1;
+        for (int l = fp64 && o->smoother == 0 ? 0 : 1; l < kMaxLevels; ++l)
             L.tile_y[l] = o->tile_rows != 0 && !tall
-                              ? o->tile_rows
-                              : (tiles16[l] <= kSmallTileLevel ? chhs::kTileYSmall : chhs::kTileY);
+                              ? (l > 0 ? o->tile_rows : chhs::kTileY)
+                              : (fp64 && tiles16[l] <= kTinyTileLevel
+                                     ? chhs::kTileYTiny
+                                     : (tiles16[l] <= kSmallTileLevel ? chhs::kTileYSmall : chhs::kTileY));
     }
-    int packed = 0;
+    int packed = 0, part0 = 0;
     for (int i = 0; i < n_inst; ++i) {
         if (!valid_problem(&p[i]) || p[i].dim != dim) return false;
         std::vector<int> ext;
@@ -746,11 +777,13 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
             if (l < tail) cell_tasks(L.B[l], i, n);
             // levels above the tail have even extents: n / 2 cells per color
             if (l < tail) cell_tasks(L.Bh[l], i, n / 2);
-            if (dim == 2) tile_tasks(L.Tall[l], i, d.nx, d.ny, L.tile_y[l]);
+            if (dim == 2) tile_tasks(L.Tall[l], i, d.nx, d.ny, L.tile_y[l], 0);
             if (dim == 2 && l < tail) {
-                tile_tasks(L.T[l], i, d.nx, d.ny, L.tile_y[l]);
-                // the autotuner may cut coarse levels into shorter tiles
-                const int ymin = l > 0 ? chhs::kTileYTiny : chhs::kTileY;
+                tile_tasks(L.T[l], i, d.nx, d.ny, L.tile_y[l], part0);
+                if (l == 0) part0 += tile_partials(d.nx, d.ny);
+                // the autotuner may cut the level into shorter tiles (the FP32
+                // finest level excepted)
+                const int ymin = l > 0 || !mixed ? chhs::kTileYTiny : chhs::kTileY;
                 L.cap_T[l] += size_t((d.nx + chhs::kTileX - 1) / chhs::kTileX) *
                               size_t((d.ny + ymin - 1) / ymin);
             }
@@ -783,6 +816,8 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     }
     // 2D smoother per level: row-streaming strips or square tiles (the same
     // choice for the FP64 and the FP32 hierarchy)
+    long cells0 = 0;        // of the largest instance
+    for (int i = 0; i < n_inst; ++i) cells0 = std::max(cells0, long(L.info[i].n0));
     if (dim == 2)
         for (int l = 0; l < kMaxLevels; ++l) {
             const int slots = strip_slots(l == 0 && !mixed, mixed);
@@ -795,16 +830,17 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
                 L.cap_S[l] = shortest.size();
             }
             L.tile_threads[l] = o->tile_threads;
-            // default: strips on the finest level (long segments, two blocks
-            // per compute unit), tiles below, where more and shorter blocks
-            // hide latency better
+            // default: strips on a large finest level (long segments, two blocks
+            // per compute unit; in mixed precision on every finest level),
+            // tiles elsewhere, where more and shorter blocks hide latency better
             // the strip kernel loads pairs of cells: every grid of the level
             // needs an even x extent
             bool even = true;
             for (int i = 0; i < n_inst; ++i) even = even && (lnx[l][i] < 0 || lnx[l][i] % 2 == 0);
             L.strip[l] = even && o->order != 1 &&
                          (o->smoother == 2 ? !L.Sall[l].empty()
-                                                   : (o->smoother == 0 && l == 0 && !L.T[l].empty()));
+                                                   : (o->smoother == 0 && l == 0 && !L.T[l].empty() &&
+                                                      (mixed || cells0 >= kStripCells)));
         }
     L.snx = lnx_t;
     if (step3d_opts(dim, o))
@@ -867,7 +903,8 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     fused_ranges(L, n_inst);
     L.partial_cap = int(std::max(L.A[0].size(), L.M0.size()));
     L.partial_t_cap =
-        int(std::max<size_t>(1, std::max({L.T[0].size(), L.S[0].size(), L.Z64[0].size()})));
+        int(std::max<size_t>(1, std::max({L.T[0].size(), L.cap_T[0], L.S[0].size(), L.cap_S[0],
+                                          L.Z64[0].size()})));
     L.off_desc = take(L.desc.size() * sizeof(LevelDesc<double>));
     L.off_desc32 = take(std::max<size_t>(1, L.desc32.size()) * sizeof(LevelDesc<float>));
     L.off_info = take(L.info.size() * sizeof(InstInfo));
@@ -907,7 +944,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         L.off_BcS.push_back(take(L.BcS[l].size() * sizeof(CellTask)));
     }
     L.off_partial = take(size_t(L.partial_cap) * chhs::kPartialStride * sizeof(double));
-    L.off_partial_t = take(size_t(L.partial_t_cap) * chhs::kPartialStride * sizeof(double));
+    L.off_partial_t = take(size_t(L.partial_t_cap) * chhs::kNormStride * sizeof(double));
     L.off_partial_f = take(std::max<size_t>(1, std::max({L.FA0.size(), L.FA0n.size(), L.FM0.size()})) *
                            chhs::kPartialStride * sizeof(double));
     // res | act_next | cycles contiguous: one readback per cycle
@@ -1063,7 +1100,7 @@ void tiled(chhs_ctx* c, const Hier<T>& H, bool all, int l, int ns, int epi, bool
             const int* thr = post && c->lay.tile_threads_post[l] > 0 ? c->lay.tile_threads_post
                                                                      : c->lay.tile_threads;
             chhs::launch_tile2d<T>(b, tt.dev, tt.n, level0, ns, epi, pro,
-                                   tile_block(all ? 0 : thr[l], tt.n), rhs,
+                                   tile_block(all ? 0 : thr[l], tt.n, std::is_same<T, double>::value), rhs,
                                    all ? c->lay.tile_y_all[l] : c->lay.tile_y[l], zero, part,
                                    c->stream);
         }
@@ -1437,7 +1474,7 @@ int autotune(chhs_ctx* c) {
         };
         std::vector<Cand> cands;
         for (int ty : {chhs::kTileY, chhs::kTileYSmall, chhs::kTileYTiny}) {
-            if (l == 0 && ty != chhs::kTileY) continue;     // the finest level has 64 x 16 tiles
+            if (l == 0 && c->mixed && ty != chhs::kTileY) continue;
             for (int nt : {256, 512, 1024}) cands.push_back({false, nt, 0, ty});
         }
         // ... or, on the FP32 finest level (mixed precision), 64 x 32 (on
@@ -1475,8 +1512,12 @@ int autotune(chhs_ctx* c) {
                 if (k.ty == L.tile_y[l]) return CHHS_OK;
                 // re-cut the level's tiles (same instance order as the plan)
                 L.T[l].clear();
+                int part = 0;
                 for (int i = 0; i < c->n_inst; ++i)
-                    if (L.snx[l][i] >= 0) tile_tasks(L.T[l], i, L.snx[l][i], L.sny[l][i], k.ty);
+                    if (L.snx[l][i] >= 0) {
+                        tile_tasks(L.T[l], i, L.snx[l][i], L.sny[l][i], k.ty, part);
+                        if (l == 0) part += tile_partials(L.snx[l][i], L.sny[l][i]);
+                    }
                 if (L.T[l].size() > L.cap_T[l]) return CHHS_E_INVAL;
                 L.tile_y[l] = k.ty;
                 c->T[l].n = int(L.T[l].size());
@@ -2418,7 +2459,7 @@ int chhs_level_kernel(chhs_ctx* c, int32_t level, int32_t* out3) {
         out3[2] = c->S[level].n;
     } else {
         out3[0] = 0;
-        out3[1] = tile_block(c->lay.tile_threads[level], c->T[level].n);
+        out3[1] = tile_block(c->lay.tile_threads[level], c->T[level].n, !c->mixed);
         out3[2] = c->T[level].n;
     }
     return CHHS_OK;

@@ -159,6 +159,74 @@ __device__ __forceinline__ float recip_ge1(float x) {
     return __builtin_fmaf(r, e, r);
 }
 
+// The same update and operator in FP64 with every rounding written out (no
+// contraction left to the compiler), for kernels of several shapes that must
+// give the same bits: cell_sums is fed the faces in the order x - 1, x + 1,
+// y - 1, y + 1 (, z - 1, z + 1).  The nonlinear term is kept as a polynomial of
+// phi: chi' = d0 + phi (c1 + 3/4 phi), chi - chi' phi = psi^3 / 4 - phi^2 (c1 + phi) / 2
+// with d0 = psi^2 / 4, c1 = psi / 2 (a third fewer operations than chi and chi'
+// apart).
+struct CellSums {
+    double sa = 0, sa2 = 0, smmu = 0, sphi = 0, sp = 0, sap = 0, samu = 0;
+    __device__ __forceinline__ void face(double gam, double psc, double psn, double mun, double pn,
+                                         double phin) {
+#pragma clang fp contract(off)
+        const double a = 0.5 * (psc + psn);
+        sa = sa + a;
+        sa2 = __builtin_fma(a, a, sa2);
+        smmu = __builtin_fma(__builtin_fma(a, gam * a, 1.0), mun, smmu);
+        sphi = sphi + phin;
+        sp = sp + pn;
+        sap = __builtin_fma(a, pn, sap);
+        samu = __builtin_fma(a, mun, samu);
+    }
+};
+__device__ __forceinline__ void cell_update(const CellSums& q, int nf, double lam, double inv_lam,
+                                            double kap, double gam, double x, double psi, double f0,
+                                            double f1, double f2, double& phi, double& mu,
+                                            double& p) {
+#pragma clang fp contract(off)
+    const double fnf = double(nf);
+    const double inv_nf = nf == 6 ? 1.0 / 6.0
+                        : (nf == 5 ? 1.0 / 5.0
+                        : (nf == 4 ? 0.25 : (nf == 3 ? 1.0 / 3.0 : (nf == 2 ? 0.5 : 1.0))));
+    const double c1 = 0.5 * psi, d0 = c1 * c1;
+    const double bb = __builtin_fma(kap, fnf, __builtin_fma(x, __builtin_fma(0.75, x, c1), d0));
+    const double ared =
+        lam * __builtin_fma(gam, __builtin_fma(-(q.sa * q.sa), inv_nf, q.sa2), fnf);
+    const double inv_det = recip_ge1(__builtin_fma(ared, bb, 1.0));
+    const double b1 = __builtin_fma(lam, q.sap, __builtin_fma(lam, q.smmu, f0));
+    const double b2 = __builtin_fma(-((0.5 * x) * x), c1 + x,
+                                    __builtin_fma(-kap, q.sphi, __builtin_fma(d0, c1, f1 + d0 * c1)));
+    const double b3 = __builtin_fma(-(lam * gam), q.samu, __builtin_fma(-lam, q.sp, f2));
+    const double b1r = __builtin_fma(q.sa * inv_nf, b3, b1);
+    mu = __builtin_fma(bb, b1r, b2) * inv_det;
+    phi = __builtin_fma(-ared, b2, b1r) * inv_det;
+    p = -(inv_nf * __builtin_fma(inv_lam, b3, (gam * q.sa) * mu));
+}
+// N(u) of one cell from the differences to its neighbours.
+struct CellDiffs {
+    double smm = 0, sap = 0, sphi = 0, sp = 0, samu = 0;
+    __device__ __forceinline__ void face(double gam, double psc, double psn, double dmu, double dp,
+                                         double dphi) {
+#pragma clang fp contract(off)
+        const double a = 0.5 * (psc + psn);
+        smm = __builtin_fma(__builtin_fma(a, gam * a, 1.0), dmu, smm);
+        sap = __builtin_fma(a, dp, sap);
+        sphi = sphi + dphi;
+        sp = sp + dp;
+        samu = __builtin_fma(a, dmu, samu);
+    }
+};
+__device__ __forceinline__ void cell_apply(const CellDiffs& q, double lam, double kap, double gam,
+                                           double x, double mu, double psi, double (&n)[3]) {
+#pragma clang fp contract(off)
+    n[0] = __builtin_fma(-lam, q.sap, __builtin_fma(-lam, q.smm, x));
+    n[1] = __builtin_fma(kap, q.sphi,
+                         __builtin_fma(-0.25 * __builtin_fma(x, x, psi * psi), x + psi, mu));
+    n[2] = __builtin_fma(lam, q.sp, (lam * gam) * q.samu);
+}
+
 // Cell-centred bi/trilinear interpolation of the coarse correction cv - cb at
 // fine cell (i, j, k) (coarse extents cnx, cny, cnz): along each axis 3/4 of
 // the parent and 1/4 of the parent's neighbour towards the cell, the parent

@@ -23,6 +23,7 @@ constexpr int kBlock = 256;          // threads per block of the cell kernels
 constexpr int kMaxTailLevels = 8;    // levels handled by the single-workgroup tail
 constexpr size_t kTailLdsBudget = 150 * 1024;   // LDS bytes the tail may stage
 constexpr int kPartialStride = 16;   // doubles per block in the partial buffer
+constexpr int kNormStride = 4;       // doubles per fused norm partial
 constexpr int kResStride = 16;       // doubles per instance in the result area
 
 // Working view of one multigrid level of one instance.
@@ -126,7 +127,9 @@ struct InstInfo {
 };
 
 struct CellTask { int inst; int cell0; };      // kBlock consecutive cells of one level
-struct TileTask { int inst; int bx; int by; }; // one tile of a 2D level
+// one tile of a 2D level; part: the norm partial of its first four rows (finest
+// level, kNormStride doubles each, the next four rows' one row of tiles further)
+struct TileTask { int inst; int bx; int by; int part; };
 struct StripTask { int inst; int sx; int y0; int y1; };   // rows [y0, y1) of strip sx
 struct Range { int begin; int end; };          // an instance's blocks in a partial buffer
 struct FoldTask { int inst; int begin; int end; };   // partials [begin, end) of one instance
@@ -287,6 +290,10 @@ template <typename T>
 void launch_tile2d(const Batch<T>& b, const TileTask* t, int nt, bool level0, int ns, int epi,
                    bool pro, int threads, bool rhs, int ty, bool zero, double* partial,
                    hipStream_t st);
+
+// The finest FP64 level's launches (level0, not rhs).
+void launch_tile2d_l0(const Batch<double>& b, const TileTask* t, int nt, int ns, int epi, bool pro,
+                      int threads, int ty, double* partial, hipStream_t st);
 
 // ---- row-streaming 2D smoothing (chhs_stream2d.hip) ---------------------------------
 // Strip sx owns columns [sx kStripWO, (sx + 1) kStripWO) and stages kStripW

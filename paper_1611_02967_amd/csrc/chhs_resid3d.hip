@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kThreads) void k_resid3d(Batch<T> bt, const Step3Ta
             for (int c = 0; c < 4; ++c) {
                 double sum = 0.0;
                 for (int k = 0; k < kThreads / 64; ++k) sum += sh[c][k];
-                partial[size_t(task) * kPartialStride + c] = sum;
+                partial[size_t(task) * kNormStride + c] = sum;
             }
     }
 }
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(kThreads) void k_refine3d(Batch<double> b64, Batch<
         for (int c = 0; c < 4; ++c) {
             double sum = 0.0;
             for (int k = 0; k < kThreads / 64; ++k) sum += sh[c][k];
-            partial[size_t(task) * kPartialStride + c] = sum;
+            partial[size_t(task) * kNormStride + c] = sum;
         }
 }
 

@@ -505,7 +505,7 @@ drained:
         for (int c = 0; c < 4; ++c) {
             double sum = 0.0;
             for (int w = 0; w < kThreads / 64; ++w) sum += red[c][w];
-            gstore(partial, task * kPartialStride + c, sum);
+            gstore(partial, task * kNormStride + c, sum);
         }
 }
 
