@@ -137,8 +137,7 @@ struct Layout {
     size_t off_A0n = 0, off_A0t = 0, off_partial_t = 0, off_A0x = 0, off_rngA0x = 0;
     size_t off_M0 = 0, off_rngM0 = 0, off_rngM0f = 0, off_FM0 = 0;
     size_t off_FA0 = 0, off_FA0n = 0, off_rngA0f = 0, off_rngA0nf = 0, off_partial_f = 0;
-    size_t off_partial = 0, off_res = 0, off_eres = 0, off_act_cycle = 0, off_act_next = 0,
-           off_cycles = 0, off_act_last = 0;
+    size_t off_partial = 0, off_res = 0, off_act = 0, off_cycles = 0, off_act_last = 0;
     std::vector<size_t> off_A, off_B, off_Bc, off_Bh, off_Bcs, off_T, off_Tall, off_S, off_Sall,
         off_Z64, off_Z32, off_ZR64, off_ZR32, off_BcS;
     int partial_cap = 0, partial_t_cap = 0;
@@ -186,12 +185,11 @@ struct chhs_ctx {
     double* partial_f = nullptr;    // folded per-cell partials
     double* partial_t = nullptr;    // norm partials of the fused finest-level launch
     double* res = nullptr;          // [n_inst][kResStride]
-    double* eres = nullptr;         // [n_inst][kResStride]
-    int* act_cycle = nullptr;
-    int* act_next = nullptr;
-    int* act_last = nullptr;        // mixed: act_cycle of the previous refinement
+    int* act = nullptr;             // instances that take part in the next cycle
+    int* act_last = nullptr;        // mixed: act of the previous refinement
     int* cycles = nullptr;
-    // pinned host mirrors of the result block (res | act_next | cycles): two
+    // pinned host mirrors of the results (res | act | cycles), written by the
+    // reduction kernel: two
     // that the cycles of the pipelined plain loop alternate between, a third
     // for the setup of a step that the loop reads with its first cycle, and
     // the current view into one of them; the energies follow the first
@@ -206,11 +204,12 @@ struct chhs_ctx {
     int cur[kMaxLevels] = {};       // current copy of u per FP64 level
     int cur32[kMaxLevels] = {};     // current copy of u per FP32 level
     bool fused_norm = false;
-    // plain 2D path with pre-smoothing: p's mean is not subtracted by a launch
-    // of its own after a cycle; the next cycle's first finest-level launch
-    // (or the tail, holding that level) subtracts it as it loads p, and the
-    // copy to the caller's arrays subtracts what is still pending
-    bool defer_shift = false;
+    // p's mean is never subtracted by a launch of its own inside a step: the
+    // equations hold p through differences only, and the copy to the caller's
+    // arrays subtracts the mean that the last reduction found (res slot 4).
+    // Where the cycle's first finest-level launch (or the tail, holding that
+    // level) can take a pending mean along as it loads p, it does
+    bool shift_in_cycle = false;
     bool loaded = false;
     // graph replay of one cycle; two slots in mixed precision (the FP64 finest
     // level alternates its copy once per refinement step)
@@ -947,13 +946,10 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     L.off_partial_t = take(size_t(L.partial_t_cap) * chhs::kNormStride * sizeof(double));
     L.off_partial_f = take(std::max<size_t>(1, std::max({L.FA0.size(), L.FA0n.size(), L.FM0.size()})) *
                            chhs::kPartialStride * sizeof(double));
-    // res | act_next | cycles contiguous: one readback per cycle
-    L.off_res = take(size_t(n_inst) * chhs::kResStride * sizeof(double) + 2 * n_inst * sizeof(int));
-    L.off_act_next = L.off_res + size_t(n_inst) * chhs::kResStride * sizeof(double);
-    L.off_cycles = L.off_act_next + n_inst * sizeof(int);
-    L.off_eres = take(size_t(n_inst) * chhs::kResStride * sizeof(double));
-    L.off_act_cycle = take(n_inst * sizeof(int));
+    L.off_res = take(size_t(n_inst) * chhs::kResStride * sizeof(double));
+    L.off_act = take(n_inst * sizeof(int));
     L.off_act_last = take(n_inst * sizeof(int));
+    L.off_cycles = take(n_inst * sizeof(int));
     L.bytes = off;
     return true;
 }
@@ -1169,7 +1165,7 @@ void smooth_steps(chhs_ctx* c, int l, int nsweeps, const int* active, int cls) {
 }
 
 // Enqueues one FAS V(nu1, nu2) cycle of one hierarchy over the batch for the
-// instances in act_cycle.  FP64: the plain form, whose finest-level post
+// instances in act.  FP64: the plain form, whose finest-level post
 // launch also yields the fused norm partials; FP32: the correction form,
 // starting from a zero correction (zero_corr; the tiled finest level's first
 // launch then takes it as implied) or from the previous cycle's.
@@ -1179,7 +1175,7 @@ template <typename T>
 void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true) {
     constexpr bool kPlain = std::is_same<T, double>::value;
     const int dim = c->dim;
-    const int* act = c->act_cycle;
+    const int* act = c->act;
     const int depth = c->lay.depth;
     const chhs_opts& o = c->opts;
     for (int d = 0; d < depth; ++d) {
@@ -1192,7 +1188,7 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true) {
             // ... and on the finest level it subtracts a deferred p shift, or,
             // for a correction cycle, takes the zero starting correction as
             // implied
-            const double* psh = kPlain && d == 0 && c->defer_shift ? c->res : nullptr;
+            const double* psh = kPlain && d == 0 && c->shift_in_cycle ? c->res : nullptr;
             const bool zero = !kPlain && d == 0 && zero_corr;
             bool first = true;
             int rem = nu1;
@@ -1209,7 +1205,7 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true) {
                 // on the finest level the first step takes the zero correction
                 // as implied (correction cycles) or subtracts a deferred p shift
                 const bool zero = !kPlain && d == 0 && zero_corr && zero_start(c);
-                const double* psh = kPlain && d == 0 && c->defer_shift ? c->res : nullptr;
+                const double* psh = kPlain && d == 0 && c->shift_in_cycle ? c->res : nullptr;
                 for (int s = 0; s < nu1; ++s)
                     step3(c, H, d, act, pre_cls, 0, zero && s == 0, s == 0 ? psh : nullptr);
             }
@@ -1249,7 +1245,7 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true) {
             tails = c->tails;
         else
             tails = c->tails32;
-        double* pend = kPlain && c->defer_shift ? c->res : nullptr;
+        double* pend = kPlain && c->shift_in_cycle ? c->res : nullptr;
         if (c->lay.own_threads > 0)
             chhs::launch_tail_own<T, !kPlain>(dim, tails, c->owners, c->n_inst, act, cycle_shape(o),
                                               pend, c->lay.own_threads, c->lay.own_lds, c->stream);
@@ -1607,11 +1603,15 @@ void fold_cells(chhs_ctx* c, bool n_only, const int* act, const double** src, co
     *rng = n_only ? c->rngA0nf : c->rngA0f;
 }
 
-// Plain FP64: one V-cycle, the residual norms (p normalised to mean zero).
-void enqueue_plain_cycle(chhs_ctx* c, bool count) {
-    const int* act = c->act_cycle;
+// Device results and flags with host mirror `buf`.
+chhs::InstResults results(chhs_ctx* c, int buf) {
+    return {c->res, c->act, c->act_last, c->cycles, c->hbuf[buf]};
+}
+
+// Plain FP64: one V-cycle and the residual norms, read into mirror `buf`.
+void enqueue_plain_cycle(chhs_ctx* c, bool count, int buf) {
+    const int* act = c->act;
     const chhs_opts& o = c->opts;
-    chhs::launch_copy_int(c->act_cycle, c->act_next, c->n_inst, c->stream);
     enqueue_vcycle(c, hier64(c));
     TimedScope t(c, CHHS_K_NORM);
     // 3D: the z-marching residual over the finest level's fused-step tasks
@@ -1624,11 +1624,9 @@ void enqueue_plain_cycle(chhs_ctx* c, bool count) {
     const double* src;
     const Range* rng;
     fold_cells(c, true, act, &src, &rng);
-    chhs::launch_inst_reduce(src, rng, c->partial_t, c->rngT0, 1, c->dinfo, act,
-                             c->act_next, c->cycles, c->res, c->n_inst, o.tol,
-                             count ? o.max_vcycles : 1 << 30, count ? 1 : 0, c->stream);
-    if (!c->defer_shift)
-        chhs::launch_shift_p(batch(c, 0, act), c->A[0].dev, c->A[0].n, c->res, c->stream);
+    chhs::launch_inst_reduce(src, rng, c->partial_t, c->rngT0, 1, c->dinfo, results(c, buf),
+                             c->n_inst, count ? chhs::kReduceCycle : chhs::kReduceUncounted, o.tol,
+                             count ? o.max_vcycles : 1 << 30, c->stream);
 }
 
 // Applies a deferred p shift to the finest level's p and clears it.
@@ -1653,18 +1651,13 @@ bool zero_start(const chhs_ctx* c) {
 // so the residual and the cycle do not change; res slot 4 holds the mean of the
 // stored p (the reduction of p'), and the copy to the caller's arrays (or
 // apply_pshift) subtracts it.
-void enqueue_refinement(chhs_ctx* c, bool count, bool add) {
-    const int* act = c->act_cycle;
+void enqueue_refinement(chhs_ctx* c, bool count, int buf) {
+    const int* act = c->act;
     const chhs_opts& o = c->opts;
-    // this refinement's flags from the last reduction; the previous ones kept
-    // for the instances that have just converged
-    chhs::launch_roll_flags(c->act_last, c->act_cycle, c->act_next, c->n_inst, c->stream);
-    if (add) {
-        const Table<CellTask>& z = zero_start(c) ? c->A0t : c->A[0];
-        chhs::launch_zero_correction(batch32(c, 0, act), z.dev, z.n, c->stream);
-        enqueue_vcycle(c, hier32(c));
-        for (int k = 1; k < o.inner_cycles; ++k) enqueue_vcycle(c, hier32(c), false);
-    }
+    const Table<CellTask>& z = zero_start(c) ? c->A0t : c->A[0];
+    chhs::launch_zero_correction(batch32(c, 0, act), z.dev, z.n, c->stream);
+    enqueue_vcycle(c, hier32(c));
+    for (int k = 1; k < o.inner_cycles; ++k) enqueue_vcycle(c, hier32(c), false);
     const bool rows = c->M0.n > 0;       // 2D: the row-marching kernel
     // 3D: z marching over the finest level's fused-step tasks (partials into
     // the fused buffer), per cell for instances whose finest level is the tail
@@ -1672,21 +1665,21 @@ void enqueue_refinement(chhs_ctx* c, bool count, bool add) {
     {
         TimedScope t(c, CHHS_K_REFINE);
         if (rows) {
-            chhs::launch_mixed_residual_rows(batch(c, 0, add ? act : nullptr), batch32(c, 0, act),
-                                             c->M0.dev, c->M0.n, add ? 1 : 0,
-                                             add ? c->act_last : nullptr, c->partial, c->stream);
+            chhs::launch_mixed_residual_rows(batch(c, 0, act), batch32(c, 0, act),
+                                             c->M0.dev, c->M0.n, 1,
+                                             c->act_last, c->partial, c->stream);
         } else if (zm) {
-            chhs::launch_refine3d(batch(c, 0, add ? act : nullptr), batch32(c, 0, act), c->Z64[0].dev,
-                                  c->Z64[0].n, add ? 1 : 0, add ? c->act_last : nullptr,
+            chhs::launch_refine3d(batch(c, 0, act), batch32(c, 0, act), c->Z64[0].dev,
+                                  c->Z64[0].n, 1, c->act_last,
                                   c->partial_t, c->stream);
             if (c->A0x.n > 0)
-                chhs::launch_mixed_residual(c->dim, batch(c, 0, add ? act : nullptr),
-                                            batch32(c, 0, act), c->A0x.dev, c->A0x.n, add ? 1 : 0,
-                                            add ? c->act_last : nullptr, c->partial, c->stream);
+                chhs::launch_mixed_residual(c->dim, batch(c, 0, act),
+                                            batch32(c, 0, act), c->A0x.dev, c->A0x.n, 1,
+                                            c->act_last, c->partial, c->stream);
         } else {
-            chhs::launch_mixed_residual(c->dim, batch(c, 0, add ? act : nullptr),
-                                        batch32(c, 0, act), c->A[0].dev, c->A[0].n, add ? 1 : 0,
-                                        add ? c->act_last : nullptr, c->partial, c->stream);
+            chhs::launch_mixed_residual(c->dim, batch(c, 0, act),
+                                        batch32(c, 0, act), c->A[0].dev, c->A[0].n, 1,
+                                        c->act_last, c->partial, c->stream);
         }
     }
     TimedScope t(c, CHHS_K_NORM);
@@ -1694,33 +1687,24 @@ void enqueue_refinement(chhs_ctx* c, bool count, bool add) {
     const double* src;
     const Range* rng;
     if (rows) {
-        fold_table(c, c->FM0, c->rngM0, c->rngM0f, add ? act : nullptr, &src, &rng);
+        fold_table(c, c->FM0, c->rngM0, c->rngM0f, act, &src, &rng);
     } else if (zm) {
         src = c->partial;
         rng = c->rngA0x;
     } else {
-        fold_cells(c, false, add ? act : nullptr, &src, &rng);
+        fold_cells(c, false, act, &src, &rng);
     }
     chhs::launch_inst_reduce(src, rng, zm ? c->partial_t : nullptr, zm ? c->rngT0 : nullptr,
-                             zm ? 1 : 0, c->dinfo, add ? act : nullptr, c->act_next, c->cycles,
-                             c->res, c->n_inst, o.tol, count ? o.max_vcycles : 1 << 30,
-                             count ? 1 : 0, c->stream);
+                             zm ? 1 : 0, c->dinfo, results(c, buf), c->n_inst,
+                             count ? chhs::kReduceCycle : chhs::kReduceUncounted, o.tol,
+                             count ? o.max_vcycles : 1 << 30, c->stream);
 }
 
-void enqueue_cycle(chhs_ctx* c, bool count) {
+void enqueue_cycle(chhs_ctx* c, bool count, int buf) {
     if (c->mixed)
-        enqueue_refinement(c, count, true);
+        enqueue_refinement(c, count, buf);
     else
-        enqueue_plain_cycle(c, count);
-}
-
-// Readback of res | act_next | cycles (contiguous on both sides) into pinned
-// mirror `buf` (enqueued).
-int enqueue_readback(chhs_ctx* c, int buf = 0) {
-    const int n = c->n_inst;
-    const size_t bytes = size_t(n) * chhs::kResStride * sizeof(double) + 2 * n * sizeof(int);
-    HIP_TRY(hipMemcpyAsync(c->hbuf[buf], c->res, bytes, hipMemcpyDeviceToHost, c->stream));
-    return CHHS_OK;
+        enqueue_plain_cycle(c, count, buf);
 }
 
 // Points the host view (hres, hact, hcyc) at mirror `buf`.
@@ -1763,9 +1747,8 @@ void ensure_graph(chhs_ctx* c, int slot, int buf) {
     bool ok = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess;
     hipGraph_t g = nullptr;
     if (ok) {
-        enqueue_cycle(c, true);
-        ok = enqueue_readback(c, buf) == CHHS_OK;
-        ok = (hipStreamEndCapture(c->stream, &g) == hipSuccess) && ok && g != nullptr;
+        enqueue_cycle(c, true, buf);
+        ok = hipStreamEndCapture(c->stream, &g) == hipSuccess && g != nullptr;
     }
     c->capturing = -1;
     if (ok && hipGraphInstantiate(&c->gexec[slot], g, nullptr, nullptr, 0) != hipSuccess) {
@@ -1785,10 +1768,8 @@ void ensure_graph(chhs_ctx* c, int slot, int buf) {
 // into mirror 0, launched directly; returns after the results are on the host.
 int run_cycle(chhs_ctx* c, bool count) {
     view_results(c, 0);
-    enqueue_cycle(c, count);
-    int rc = check_launch();
-    if (rc) return rc;
-    rc = enqueue_readback(c);
+    enqueue_cycle(c, count, 0);
+    const int rc = check_launch();
     if (rc) return rc;
     return sync_results(c);
 }
@@ -1854,9 +1835,8 @@ int run_cycles(chhs_ctx* c, bool setup_pending = false) {
             HIP_TRY(hipGraphLaunch(c->gexec[s], c->stream));
             if (c->mixed) c->cur[0] ^= 1;    // as the captured step does
         } else {
-            enqueue_cycle(c, true);
-            int rc = check_launch();
-            if (rc == CHHS_OK) rc = enqueue_readback(c, s);
+            enqueue_cycle(c, true, s);
+            const int rc = check_launch();
             if (rc) return rc;
         }
         HIP_TRY(hipEventRecord(c->cycle_done[s], c->stream));
@@ -1923,9 +1903,6 @@ int setup(chhs_ctx* c, const double* phi_prev, const double* phi_cur, const doub
     const int dim = c->dim;
     {
         TimedScope t(c, CHHS_K_SETUP);
-        chhs::launch_fill_int(c->act_next, c->n_inst, 1, c->stream);
-        chhs::launch_fill_int(c->cycles, c->n_inst, 0, c->stream);
-        chhs::launch_copy_int(c->act_cycle, c->act_next, c->n_inst, c->stream);
         // the initial residual's norm partials in the same pass (mixed
         // precision: also the FP32 frozen fields of the finest level and the
         // residual as the first correction cycle's right-hand side)
@@ -1946,43 +1923,32 @@ int setup(chhs_ctx* c, const double* phi_prev, const double* phi_cur, const doub
                                                c->lay.chain_from, c->stream);
         }
     }
-    if (c->mixed) {
-        // the residual of the initial guess came with the setup pass: its
-        // norms and the flags, as a refinement step without a correction
-        // would leave them (u stays in the current FP64 copy)
-        TimedScope t(c, CHHS_K_NORM);
-        chhs::launch_roll_flags(c->act_last, c->act_cycle, c->act_next, c->n_inst, c->stream);
-        const double* src;
-        const Range* rng;
-        fold_cells(c, false, nullptr, &src, &rng);
-        chhs::launch_inst_reduce(src, rng, nullptr, nullptr, 0, c->dinfo, nullptr, c->act_next,
-                                 c->cycles, c->res, c->n_inst, c->opts.tol, 1 << 30, 0, c->stream);
-    } else {
+    {
+        // the residual of the initial guess came with the setup pass: its norms
+        // and the flags of the first cycle (mixed precision: as a refinement
+        // step without a correction would leave them; u stays in the current
+        // FP64 copy)
         TimedScope t(c, CHHS_K_NORM);
         const double* src;
         const Range* rng;
         fold_cells(c, false, nullptr, &src, &rng);
-        chhs::launch_inst_reduce(src, rng, nullptr, nullptr, 0, c->dinfo, nullptr,
-                                 c->act_next, c->cycles, c->res, c->n_inst, c->opts.tol,
-                                 c->opts.max_vcycles, 0, c->stream);
-        if (!c->defer_shift)
-            chhs::launch_shift_p(batch(c, 0, nullptr), c->A[0].dev, c->A[0].n, c->res, c->stream);
+        chhs::launch_inst_reduce(src, rng, nullptr, nullptr, 0, c->dinfo, results(c, wait ? 0 : 2),
+                                 c->n_inst, chhs::kReduceSetup, c->opts.tol,
+                                 c->mixed ? 1 << 30 : c->opts.max_vcycles, c->stream);
     }
-    if (c->defer_shift && !defer) apply_pshift(c);
+    if (!defer) apply_pshift(c);
     int rc = check_launch();
     if (rc) return rc;
     c->loaded = true;
-    if (!wait) return enqueue_readback(c, 2);
+    if (!wait) return CHHS_OK;
     view_results(c, 0);
-    rc = enqueue_readback(c, 0);
-    if (rc) return rc;
     return sync_results(c);
 }
 
 const double* hres_of(chhs_ctx* c, int i) { return c->hres + size_t(i) * chhs::kResStride; }
 
-// Enqueues the energies (per instance, kResStride doubles each) and their
-// copy into pinned host memory `dst`: workspace mode (ws != 0: the finest
+// Enqueues the energies (per instance, kResStride doubles each), written into
+// pinned host memory `dst`: workspace mode (ws != 0: the finest
 // level's iterate, phi^m and the flow terms) or caller arrays.
 // copy (ws only): the step's copy into the caller's arrays in the same pass.
 int enqueue_energies(chhs_ctx* c, int ws, const double* phi, const double* q, double* dst,
@@ -1990,25 +1956,19 @@ int enqueue_energies(chhs_ctx* c, int ws, const double* phi, const double* q, do
     {
         TimedScope t(c, CHHS_K_SETUP);
         Batch<double> b = batch(c, 0, nullptr);
-        b.pshift = c->defer_shift ? c->res : nullptr;
+        b.pshift = c->res;
         chhs::launch_energy_partials(c->dim, b, c->A[0].dev, c->A[0].n, c->dinfo, ws, phi, q,
                                      c->partial, c->stream, copy);
         // instances with more than kFold partials: folded in runs first, so
         // that one workgroup per instance reads a few partials
         if (c->FA0.n > 0) {
             chhs::launch_fold_energy(c->partial, c->FA0.dev, c->FA0.n, c->partial_f, c->stream);
-            chhs::launch_energy_reduce(c->partial_f, c->rngA0f, c->dinfo, c->eres, c->n_inst,
-                                       c->stream);
+            chhs::launch_energy_reduce(c->partial_f, c->rngA0f, c->dinfo, dst, c->n_inst, c->stream);
         } else {
-            chhs::launch_energy_reduce(c->partial, c->rngA0, c->dinfo, c->eres, c->n_inst,
-                                       c->stream);
+            chhs::launch_energy_reduce(c->partial, c->rngA0, c->dinfo, dst, c->n_inst, c->stream);
         }
     }
-    int rc = check_launch();
-    if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(dst, c->eres, size_t(c->n_inst) * chhs::kResStride * sizeof(double),
-                           hipMemcpyDeviceToHost, c->stream));
-    return CHHS_OK;
+    return check_launch();
 }
 
 // Energies into heres (per instance), waited for.
@@ -2101,7 +2061,7 @@ int step_loop(chhs_ctx* c, double* phi_prev, double* phi_cur, double* mu, double
             for (int i = 0; i < n; ++i) fill_energies(st[i], c->heres + size_t(i) * chhs::kResStride);
         } else {
             Batch<double> bo = batch(c, 0, nullptr);
-            bo.pshift = c->defer_shift ? c->res : nullptr;
+            bo.pshift = c->res;
             chhs::launch_copy_out(bo, c->A[0].dev, c->A[0].n, c->dinfo, phi_prev, phi_cur, mu, p,
                                   c->stream);
         }
@@ -2217,10 +2177,8 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
     c->rngA0f = reinterpret_cast<Range*>(b + L.off_rngA0f);
     c->rngA0nf = reinterpret_cast<Range*>(b + L.off_rngA0nf);
     c->res = reinterpret_cast<double*>(b + L.off_res);
-    c->eres = reinterpret_cast<double*>(b + L.off_eres);
-    c->act_cycle = reinterpret_cast<int*>(b + L.off_act_cycle);
+    c->act = reinterpret_cast<int*>(b + L.off_act);
     c->act_last = reinterpret_cast<int*>(b + L.off_act_last);
-    c->act_next = reinterpret_cast<int*>(b + L.off_act_next);
     c->cycles = reinterpret_cast<int*>(b + L.off_cycles);
     hipStream_t st = c->stream;
     if (c->mixed && hipMemcpyAsync(c->ddesc32, L.desc32.data(),
@@ -2300,8 +2258,7 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
     view_results(c, 0);
     c->heres = c->hbuf[0] + nres + nint;
     c->fused_norm = !c->mixed && c->dim == 2 && o->nu2 > 0 && o->order != 1;
-    // the mixed path never subtracts p's mean inside its cycles
-    c->defer_shift = c->mixed || (tiled2d(c) && o->nu1 > 0);
+    c->shift_in_cycle = !c->mixed && tiled2d(c) && o->nu1 > 0;
     if (hipStreamSynchronize(st) != hipSuccess) return fail(CHHS_E_HIP);
     if (o->autotune && o->smoother == 0 && c->dim == 2 && o->nu1 > 0 && o->nu2 > 0 &&
         o->order != 1) {
@@ -2314,7 +2271,7 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
     }
     // 3D plain FP64 with the fused step on the finest level: its first
     // pre-smoothing launch subtracts p's pending mean as it loads p
-    if (!c->mixed && z3_at(c, 0) && o->nu1 > 0) c->defer_shift = true;
+    if (!c->mixed && z3_at(c, 0) && o->nu1 > 0) c->shift_in_cycle = true;
     {
         // the per-step log of chhs_step_log, reserved up front
         const size_t per_step = size_t(n_inst) * chhs::kResStride * sizeof(double);
@@ -2338,15 +2295,13 @@ int chhs_fas_vcycle(chhs_ctx* c, double* res_norm_host) {
     if (c == nullptr) return CHHS_E_INVAL;
     if (!c->loaded) return CHHS_E_STATE;
     // every instance takes part, whatever its convergence state
-    chhs::launch_fill_int(c->act_next, c->n_inst, 1, c->stream);
+    chhs::launch_fill_int(c->act, c->n_inst, 1, c->stream);
     int rc = run_cycle(c, false);
     if (rc) return rc;
     // the level's fields after this call hold the normalised p
-    if (c->defer_shift) {
-        apply_pshift(c);
-        rc = check_launch();
-        if (rc) return rc;
-    }
+    apply_pshift(c);
+    rc = check_launch();
+    if (rc) return rc;
     bool finite = true;
     for (int i = 0; i < c->n_inst; ++i) {
         if (res_norm_host) res_norm_host[i] = hres_of(c, i)[3];
@@ -2363,12 +2318,10 @@ int chhs_residual_norms(chhs_ctx* c, double* out_host) {
     const double* src;
     const Range* rng;
     fold_cells(c, false, nullptr, &src, &rng);
-    chhs::launch_inst_reduce(src, rng, nullptr, nullptr, 0, c->dinfo, nullptr,
-                             c->act_next, c->cycles, c->res, c->n_inst, c->opts.tol, 1 << 30, 0,
-                             c->stream);
+    view_results(c, 0);
+    chhs::launch_inst_reduce(src, rng, nullptr, nullptr, 0, c->dinfo, results(c, 0), c->n_inst,
+                             chhs::kReduceQuery, c->opts.tol, 1 << 30, c->stream);
     int rc = check_launch();
-    if (rc) return rc;
-    rc = enqueue_readback(c);
     if (rc) return rc;
     rc = sync_results(c);
     if (rc) return rc;
@@ -2380,7 +2333,7 @@ int chhs_get_solution(chhs_ctx* c, double* phi, double* mu, double* p) {
     if (c == nullptr) return CHHS_E_INVAL;
     if (!c->loaded) return CHHS_E_STATE;
     Batch<double> b = batch(c, 0, nullptr);
-    b.pshift = c->defer_shift ? c->res : nullptr;
+    b.pshift = c->res;
     chhs::launch_get_solution(b, c->A[0].dev, c->A[0].n, c->dinfo, phi, mu, p, c->stream);
     return check_launch();
 }

@@ -212,12 +212,6 @@ void launch_mixed_residual(int dim, const Batch<double>& b64, const Batch<float>
 // partial[block][0..3] = sum R_phi^2, R_mu^2, R_p^2, p over the block's cells
 void launch_residual_partials(int dim, const Batch<double>& b, const CellTask* t, int nt,
                               double* partial, hipStream_t st);
-// Per instance i (one block each), if active[i] (or active == nullptr): sums
-// its partials in a fixed order -- partial_t[ranges_t[i]] when use_fused and
-// info[i].fused, else partial[ranges[i]]; res[i*kResStride + 0..3] = ||R_phi||,
-// ||R_mu||, ||R_p||, combined norm; 4 = mean(p); 5 = 1 if the norm is not
-// finite; count != 0: cycles[i] += 1; act_next[i] = norm > tol, finite and
-// cycles[i] < max_cycles.  Inactive instances keep their results.
 // dst[q] = the sum of src[t[q].begin .. t[q].end) (4 doubles per partial, in
 // index order within each thread's stride, then over the block), for the
 // tasks of active instances.
@@ -225,10 +219,27 @@ void launch_fold_partials(const double* src, const FoldTask* t, int nt, const in
                           double* dst, hipStream_t st);
 // The same for the energy partials (eight sums and a maximum each).
 void launch_fold_energy(const double* src, const FoldTask* t, int nt, double* dst, hipStream_t st);
+// Results and flags of the instances: res[i * kResStride + 0..3] = ||R_phi||,
+// ||R_mu||, ||R_p||, combined norm; 4 = mean(p); 5 = 1 if the norm is not
+// finite; act: takes part in the next cycle; last: took part in this one (mixed
+// precision); mirror: pinned host copy, res of all instances | act | cycles.
+struct InstResults {
+    double* res;
+    int *act, *last, *cycles;
+    double* mirror;
+};
+// Per instance i (one block each): sums its partials in a fixed order --
+// partial_t[ranges_t[i]] when use_fused and info[i].fused, else
+// partial[ranges[i]] -- into res and the mirror.  kReduceSetup: cycles = 0, last
+// = 1; kReduceCycle: of the active instances only, cycles += 1
+// (kReduceUncounted: not counted), last = act before; both: act = norm > tol,
+// finite and cycles < max_cycles.  Inactive instances keep their results, which
+// are written to the mirror again.  kReduceQuery: the results alone.
+enum { kReduceSetup = 0, kReduceCycle = 1, kReduceUncounted = 2, kReduceQuery = 3 };
 void launch_inst_reduce(const double* partial, const Range* ranges, const double* partial_t,
                         const Range* ranges_t, int use_fused, const InstInfo* info,
-                        const int* active, int* act_next, int* cycles, double* res, int n_inst,
-                        double tol, int max_cycles, int count, hipStream_t st);
+                        const InstResults& out, int n_inst, int mode, double tol, int max_cycles,
+                        hipStream_t st);
 // p -= mean(p) (res slot 4) on the finest level of active instances.
 // res[i * kResStride + 4] = 0 for every instance (a deferred p shift applied)
 void launch_clear_pshift(double* res, int n_inst, hipStream_t st);
@@ -249,7 +260,7 @@ void launch_energy_partials(int dim, const Batch<double>& b, const CellTask* t, 
                             const InstInfo* info, int ws, const double* phi, const double* q,
                             double* partial, hipStream_t st, const CopyOut* copy = nullptr);
 // Per instance: out[i*kResStride + 0..5] = mass, E_h, F_h, s||grad mu||^2,
-// (s/gamma)||u||^2, max |phi|.
+// (s/gamma)||u||^2, max |phi| (out: pinned host memory).
 void launch_energy_reduce(const double* partial, const Range* ranges, const InstInfo* info,
                           double* out, int n_inst, hipStream_t st);
 // State rotation into packed caller arrays: phi_prev <- phi_cur, phi_cur <- phi,
@@ -260,9 +271,6 @@ void launch_copy_out(const Batch<double>& b, const CellTask* t, int nt, const In
 void launch_get_solution(const Batch<double>& b, const CellTask* t, int nt, const InstInfo* info,
                          double* phi, double* mu, double* p, hipStream_t st);
 void launch_fill_int(int* dst, int n, int value, hipStream_t st);
-void launch_copy_int(int* dst, const int* src, int n, hipStream_t st);
-// last <- cur, cur <- next (per-instance flags)
-void launch_roll_flags(int* last, int* cur, const int* next, int n, hipStream_t st);
 
 // ---- tiled 2D smoothing (chhs_tile2d.hip) ------------------------------------------
 // Tiles are 64 x 16 cells, or on coarse levels 64 x 8 or 64 x 4 (more,

@@ -763,17 +763,34 @@ __global__ __launch_bounds__(kBlock) void k_fold_energy(const double* __restrict
     }
 }
 
+// Latency: one workgroup per instance at the end of every cycle, on the path to
+// the host's stopping test.  It therefore also turns the flags over for the
+// next cycle and writes the instance's results into the host's pinned mirror
+// itself: the flag copy and the readback were two more launches (3.5 + 3.7 us
+// and their gaps at 512^2, of 150 us a cycle).
 __global__ __launch_bounds__(kBlock) void k_inst_reduce(const double* __restrict__ partial,
                                                         const Range* __restrict__ ranges,
                                                         const double* __restrict__ partial_t,
                                                         const Range* __restrict__ ranges_t,
                                                         int use_fused,
                                                         const InstInfo* __restrict__ info,
-                                                        const int* active, int* act_next,
-                                                        int* cycles, double* res, double tol,
-                                                        int max_cycles, int count) {
+                                                        InstResults out, int mode, double tol,
+                                                        int max_cycles) {
     const int i = blockIdx.x;
-    if (inactive(active, i)) return;
+    double* r = out.res + i * kResStride;
+    double* m = out.mirror + i * kResStride;
+    int* mflags = reinterpret_cast<int*>(out.mirror + size_t(gridDim.x) * kResStride);
+    const bool cycle = mode == kReduceCycle || mode == kReduceUncounted;
+    if (cycle && out.act[i] == 0) {
+        // unchanged results; the mirrors alternate, so this one gets them too
+        if (threadIdx.x < 6) m[threadIdx.x] = r[threadIdx.x];
+        if (threadIdx.x == 0) {
+            out.last[i] = 0;
+            mflags[i] = 0;
+            mflags[gridDim.x + i] = out.cycles[i];
+        }
+        return;
+    }
     const InstInfo in = info[i];
     const bool fused = use_fused && in.fused;
     const Range rg = fused ? ranges_t[i] : ranges[i];
@@ -792,17 +809,20 @@ __global__ __launch_bounds__(kBlock) void k_inst_reduce(const double* __restrict
     if (in.dim == 3) hd *= in.h;
     const double a = s[0] * hd, bb = s[1] * hd, c = s[2] * hd;
     const double tot = sqrt(a + bb + c);
-    double* r = res + i * kResStride;
-    r[0] = sqrt(a);
-    r[1] = sqrt(bb);
-    r[2] = sqrt(c);
-    r[3] = tot;
-    r[4] = s[3] / double(in.n0);
     const bool finite = tot == tot && tot < 1e300;
-    r[5] = finite ? 0.0 : 1.0;
-    int cyc = cycles[i];
-    if (count) cycles[i] = ++cyc;
-    act_next[i] = (finite && tot > tol && cyc < max_cycles) ? 1 : 0;
+    const double o[6] = {sqrt(a), sqrt(bb), sqrt(c), tot, s[3] / double(in.n0), finite ? 0.0 : 1.0};
+    for (int k = 0; k < 6; ++k) {
+        r[k] = o[k];
+        m[k] = o[k];
+    }
+    if (mode == kReduceQuery) return;
+    const int cyc = mode == kReduceSetup ? 0 : out.cycles[i] + (mode == kReduceCycle ? 1 : 0);
+    const int act = (finite && tot > tol && cyc < max_cycles) ? 1 : 0;
+    out.cycles[i] = cyc;
+    out.last[i] = 1;
+    out.act[i] = act;
+    mflags[i] = act;
+    mflags[gridDim.x + i] = cyc;
 }
 
 __global__ __launch_bounds__(kBlock) void k_shift_p(Batch<double> b, const CellTask* __restrict__ t,
@@ -1030,19 +1050,6 @@ __global__ __launch_bounds__(kBlock) void k_fill_int(int* dst, int n, int value)
     if (i < n) dst[i] = value;
 }
 
-__global__ __launch_bounds__(kBlock) void k_copy_int(int* dst, const int* src, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = src[i];
-}
-
-__global__ __launch_bounds__(kBlock) void k_roll_flags(int* last, int* cur, const int* next, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        last[i] = cur[i];
-        cur[i] = next[i];
-    }
-}
-
 inline int blocks_for(int n) { return (n + kBlock - 1) / kBlock; }
 
 }  // namespace
@@ -1236,11 +1243,10 @@ void launch_fold_energy(const double* src, const FoldTask* t, int nt, double* ds
 
 void launch_inst_reduce(const double* partial, const Range* ranges, const double* partial_t,
                         const Range* ranges_t, int use_fused, const InstInfo* info,
-                        const int* active, int* act_next, int* cycles, double* res, int n_inst,
-                        double tol, int max_cycles, int count, hipStream_t st) {
+                        const InstResults& out, int n_inst, int mode, double tol, int max_cycles,
+                        hipStream_t st) {
     hipLaunchKernelGGL(k_inst_reduce, dim3(n_inst), dim3(kBlock), 0, st, partial, ranges,
-                       partial_t, ranges_t, use_fused, info, active, act_next, cycles, res, tol,
-                       max_cycles, count);
+                       partial_t, ranges_t, use_fused, info, out, mode, tol, max_cycles);
 }
 
 void launch_clear_pshift(double* res, int n_inst, hipStream_t st) {
@@ -1286,15 +1292,6 @@ void launch_get_solution(const Batch<double>& b, const CellTask* t, int nt, cons
 
 void launch_fill_int(int* dst, int n, int value, hipStream_t st) {
     if (n > 0) hipLaunchKernelGGL(k_fill_int, dim3(blocks_for(n)), dim3(kBlock), 0, st, dst, n, value);
-}
-
-void launch_copy_int(int* dst, const int* src, int n, hipStream_t st) {
-    if (n > 0) hipLaunchKernelGGL(k_copy_int, dim3(blocks_for(n)), dim3(kBlock), 0, st, dst, src, n);
-}
-
-void launch_roll_flags(int* last, int* cur, const int* next, int n, hipStream_t st) {
-    if (n > 0)
-        hipLaunchKernelGGL(k_roll_flags, dim3(blocks_for(n)), dim3(kBlock), 0, st, last, cur, next, n);
 }
 
 }  // namespace chhs
