@@ -106,6 +106,8 @@ struct Layout {
     std::vector<int> own;
     int own_threads = 0;
     size_t own_lds = 0;
+    int tail_parts = 0;         // instances whose finest level is there (FP64): their norm
+                                // partials come first in partial_t
     std::vector<TailOwner> owners;
     std::vector<TailDesc<double>> tails;
     std::vector<TailDesc<float>> tails32;
@@ -207,8 +209,8 @@ struct chhs_ctx {
     // p's mean is never subtracted by a launch of its own inside a step: the
     // equations hold p through differences only, and the copy to the caller's
     // arrays subtracts the mean that the last reduction found (res slot 4).
-    // Where the cycle's first finest-level launch (or the tail, holding that
-    // level) can take a pending mean along as it loads p, it does
+    // Where the cycle's first finest-level launch can take a pending mean along
+    // as it loads p, it does
     bool shift_in_cycle = false;
     bool loaded = false;
     // graph replay of one cycle; two slots in mixed precision (the FP64 finest
@@ -360,6 +362,8 @@ void tail_owners(int dim, int top, int nlev, int order, const LevelDesc<T>* desc
     d.finest = top == 0 ? 1 : 0;
     d.cubic = order == 1 ? 1 : 0;
     d.single = d.joined = 0;
+    d.part = 0;
+    d.top_waves = (chhs::own_pairs(desc[top].nx, desc[top].ny, desc[top].nz) + 63) / 64;
     int t = 0, off = 0, prev_wave = -1;
     for (int l = top; l < nlev; ++l) {
         const LevelDesc<T>& D = desc[l];
@@ -524,7 +528,7 @@ void task_ranges(std::vector<Range>& r, int n_inst, const std::vector<Task>& tas
     }
 }
 
-void fused_ranges(Layout& L, int n_inst) {
+void level0_ranges(Layout& L, int n_inst) {
     if (L.strip[0])
         task_ranges(L.rngT0, n_inst, L.S[0]);
     else if (!L.T[0].empty()) {
@@ -539,6 +543,20 @@ void fused_ranges(Layout& L, int n_inst) {
     }
     else
         task_ranges(L.rngT0, n_inst, L.Z64[0]);     // 3D
+}
+
+// The partials of instances held by the tail come first.
+void fused_ranges(Layout& L, int n_inst) {
+    level0_ranges(L, n_inst);
+    int k = 0;
+    for (int i = 0; i < n_inst; ++i)
+        if (L.info[i].fused && L.info[i].tail == 0) {
+            L.rngT0[i] = Range{k, k + 1};
+            ++k;
+        } else {
+            L.rngT0[i].begin += L.tail_parts;
+            L.rngT0[i].end += L.tail_parts;
+        }
 }
 
 // 3D levels above the tail may be smoothed by the fused z-marching step kernel
@@ -708,9 +726,12 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         // the finest level's norm partials: from the fused 2D post launch, or
         // (3D) from the z-marching residual kernel over the fused-step tasks
         // (the mixed 3D path: from the z-marching refinement step)
+        // or, held by the tail with owner threads, from the tail itself
         in.fused = (!first && tail > 0 &&
-                    ((dim == 2 && !mixed && o->nu2 > 0) || (dim == 3 && step3d_opts(dim, o))))
+                    ((dim == 2 && !mixed && o->nu2 > 0) || (dim == 3 && step3d_opts(dim, o)))) ||
+                           (!mixed && tail == 0 && L.own.back() != 0)
                        ? 1 : 0;
+        if (!mixed && tail == 0 && L.own.back()) ++L.tail_parts;
         in.h = p[i].h;
         in.eps = p[i].eps;
         in.gamma = p[i].gamma;
@@ -802,6 +823,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     L.owners.assign(size_t(n_inst) * L.own_threads, TailOwner{});
     L.tails.assign(mixed ? 0 : n_inst, TailDesc<double>{});
     L.tails32.assign(mixed ? n_inst : 0, TailDesc<float>{});
+    int tail_part = 0;
     for (int i = 0; base != nullptr && i < n_inst; ++i) {
         if (!L.own[i]) continue;
         TailOwner* own = &L.owners[size_t(i) * L.own_threads];
@@ -812,6 +834,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         else
             tail_owners(dim, in.tail, in.nlev, in.order, &L.desc[size_t(i) * kMaxLevels], own,
                         L.tails[i]);
+        if (!mixed && in.tail == 0) L.tails[i].part = tail_part++;
     }
     // 2D smoother per level: row-streaming strips or square tiles (the same
     // choice for the FP64 and the FP32 hierarchy)
@@ -902,8 +925,8 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     fused_ranges(L, n_inst);
     L.partial_cap = int(std::max(L.A[0].size(), L.M0.size()));
     L.partial_t_cap =
-        int(std::max<size_t>(1, std::max({L.T[0].size(), L.cap_T[0], L.S[0].size(), L.cap_S[0],
-                                          L.Z64[0].size()})));
+        L.tail_parts + int(std::max<size_t>(1, std::max({L.T[0].size(), L.cap_T[0], L.S[0].size(),
+                                                         L.cap_S[0], L.Z64[0].size()})));
     L.off_desc = take(L.desc.size() * sizeof(LevelDesc<double>));
     L.off_desc32 = take(std::max<size_t>(1, L.desc32.size()) * sizeof(LevelDesc<float>));
     L.off_info = take(L.info.size() * sizeof(InstInfo));
@@ -1075,6 +1098,16 @@ struct Hier {
 Hier<double> hier64(chhs_ctx* c) { return {c->ddesc, &c->lay.desc, c->cur}; }
 Hier<float> hier32(chhs_ctx* c) { return {c->ddesc32, &c->lay.desc32, c->cur32}; }
 
+// Device results and flags with host mirror `buf`.
+chhs::InstResults results(chhs_ctx* c, int buf) {
+    return {c->res, c->act, c->act_last, c->cycles, c->hbuf[buf]};
+}
+
+// The norm partials of the finest level's launches.
+double* level0_partials(chhs_ctx* c) {
+    return c->partial_t + size_t(c->lay.tail_parts) * chhs::kNormStride;
+}
+
 // One 2D smoothing launch on level l (row-streaming strips or tiles, as
 // planned; all = every instance, else those whose tail starts below l);
 // flips the level's current copy.
@@ -1085,7 +1118,7 @@ void tiled(chhs_ctx* c, const Hier<T>& H, bool all, int l, int ns, int epi, bool
     Batch<T> b = make_batch(H.dev, H.cur, l, active);
     b.pshift = pshift;
     const bool level0 = std::is_same<T, double>::value && l == 0;
-    double* part = epi == 2 ? c->partial_t : nullptr;
+    double* part = epi == 2 ? level0_partials(c) : nullptr;
     {
         TimedScope t(c, cls);
         if (c->lay.strip[l]) {
@@ -1168,11 +1201,12 @@ void smooth_steps(chhs_ctx* c, int l, int nsweeps, const int* active, int cls) {
 // instances in act.  FP64: the plain form, whose finest-level post
 // launch also yields the fused norm partials; FP32: the correction form,
 // starting from a zero correction (zero_corr; the tiled finest level's first
-// launch then takes it as implied) or from the previous cycle's.
+// launch then takes it as implied) or from the previous cycle's.  solve > 0
+// (whole_in_tail): the step's cycles, at most that many, results to mirror buf.
 bool zero_start(const chhs_ctx* c);
 
 template <typename T>
-void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true) {
+void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int solve = 0, int buf = 0) {
     constexpr bool kPlain = std::is_same<T, double>::value;
     const int dim = c->dim;
     const int* act = c->act;
@@ -1245,12 +1279,14 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true) {
             tails = c->tails;
         else
             tails = c->tails32;
-        double* pend = kPlain && c->shift_in_cycle ? c->res : nullptr;
+        const chhs::TailSolve ts{kPlain && c->lay.tail_parts > 0 ? c->partial_t : nullptr, solve, o.tol,
+                                 c->dinfo, results(c, buf)};
         if (c->lay.own_threads > 0)
             chhs::launch_tail_own<T, !kPlain>(dim, tails, c->owners, c->n_inst, act, cycle_shape(o),
-                                              pend, c->lay.own_threads, c->lay.own_lds, c->stream);
+                                              ts, c->lay.own_threads, c->lay.own_lds,
+                                              c->stream);
         chhs::launch_tail<T, !kPlain>(dim, H.dev, c->dinfo, c->tail_insts,
-                                      int(c->lay.tail_insts.size()), act, 0u, cycle_shape(o), pend,
+                                      int(c->lay.tail_insts.size()), act, 0u, cycle_shape(o),
                                       c->lay.tail_lds, c->stream);
     }
     const bool bil = o.prolong == 1;
@@ -1603,13 +1639,18 @@ void fold_cells(chhs_ctx* c, bool n_only, const int* act, const double** src, co
     *rng = n_only ? c->rngA0nf : c->rngA0f;
 }
 
-// Device results and flags with host mirror `buf`.
-chhs::InstResults results(chhs_ctx* c, int buf) {
-    return {c->res, c->act, c->act_last, c->cycles, c->hbuf[buf]};
+// Plain FP64, every instance's finest level held by the tail with owner threads:
+// one launch runs the counted cycles of a step (16^2: 333 -> 150 us a step).
+bool whole_in_tail(const chhs_ctx* c) {
+    return !c->mixed && c->lay.tail_parts == c->n_inst && c->opts.timing == 0;
 }
 
 // Plain FP64: one V-cycle and the residual norms, read into mirror `buf`.
 void enqueue_plain_cycle(chhs_ctx* c, bool count, int buf) {
+    if (count && whole_in_tail(c)) {
+        enqueue_vcycle(c, hier64(c), true, c->opts.max_vcycles, buf);
+        return;
+    }
     const int* act = c->act;
     const chhs_opts& o = c->opts;
     enqueue_vcycle(c, hier64(c));
@@ -1617,7 +1658,7 @@ void enqueue_plain_cycle(chhs_ctx* c, bool count, int buf) {
     // 3D: the z-marching residual over the finest level's fused-step tasks
     if (c->dim == 3 && c->Z64[0].n > 0)
         chhs::launch_residual3d_partials(batch(c, 0, act), c->Z64[0].dev, c->Z64[0].n,
-                                         c->partial_t, c->stream);
+                                         level0_partials(c), c->stream);
     // instances without a fused finest-level norm: per-cell residual partials
     chhs::launch_residual_partials(c->dim, batch(c, 0, act), c->A0n.dev, c->A0n.n, c->partial,
                                    c->stream);
@@ -1671,7 +1712,7 @@ void enqueue_refinement(chhs_ctx* c, bool count, int buf) {
         } else if (zm) {
             chhs::launch_refine3d(batch(c, 0, act), batch32(c, 0, act), c->Z64[0].dev,
                                   c->Z64[0].n, 1, c->act_last,
-                                  c->partial_t, c->stream);
+                                  level0_partials(c), c->stream);
             if (c->A0x.n > 0)
                 chhs::launch_mixed_residual(c->dim, batch(c, 0, act),
                                             batch32(c, 0, act), c->A0x.dev, c->A0x.n, 1,
@@ -1847,7 +1888,7 @@ int run_cycles(chhs_ctx* c, bool setup_pending = false) {
     int rc = launch();
     if (rc) return rc;
     for (;;) {
-        if (nq == 1 && (setup_pending || expect_more(c, rho))) {
+        if (nq == 1 && !whole_in_tail(c) && (setup_pending || expect_more(c, rho))) {
             rc = launch();
             if (rc) return rc;
         }

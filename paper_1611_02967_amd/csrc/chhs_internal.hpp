@@ -358,7 +358,7 @@ int prepare_tail(int dim, size_t lds_bytes);
 template <typename T, bool CORR>
 void launch_tail(int dim, const LevelDesc<T>* desc, const InstInfo* info, const int* insts,
                  int ninst, const int* active, unsigned cur_mask, const CycleShape& shape,
-                 double* pend, size_t lds_bytes, hipStream_t st);
+                 size_t lds_bytes, hipStream_t st);
 
 // ---- the same with an owner thread per pair of cells (chhs_tail_own.hip) -----------
 // LDS of one tail level, in values: the records of u and one of zeros, the
@@ -366,7 +366,7 @@ void launch_tail(int dim, const LevelDesc<T>* desc, const InstInfo* info, const 
 __host__ __device__ constexpr int own_words(int n, bool corr) { return (corr ? 11 : 10) * n + 3; }
 // Threads at most (the kernel's registers per lane, without spilling).
 constexpr int own_max_threads(int dim, bool corr) {
-    return dim == 2 ? (corr ? 1024 : 768) : (corr ? 768 : 512);
+    return corr ? 1024 : (dim == 2 ? 768 : 512);
 }
 // Owner threads: every pair of x-adjacent cells of every tail level has one
 // (the last pair of an odd row holds one cell).  Levels are placed finest
@@ -412,13 +412,25 @@ struct TailDesc {
     T lam, kap, gamma;
     int levels, finest, cubic;     // levels 0: the instance is not worked here
     unsigned single, joined;
+    int top_waves, part;           // waves of the top level's owners; its norm partial (finest level)
+};
+// Norm of a finest level held by the tail (FP64): partial (kNormStride doubles
+// at TailDesc::part) and, with cycles > 0, up to that many cycles in one launch,
+// an instance's until its norm is <= tol, its results written to out
+// (finest levels only, every instance).  partial null: no norm.
+struct TailSolve {
+    double* partial;
+    int cycles;
+    double tol;
+    const InstInfo* info;
+    InstResults out;
 };
 // One workgroup per instance (threads: at least every instance's owner threads,
 // and the stride of owners): the V-cycle over levels info.tail ..
 // info.nlev - 1 of that instance, always on copy 0 of u.
 template <typename T, bool CORR>
 void launch_tail_own(int dim, const TailDesc<T>* tails, const TailOwner* owners, int ninst,
-                 const int* active, const CycleShape& shape, double* pend, int threads,
-                 size_t lds_bytes, hipStream_t st);
+                 const int* active, const CycleShape& shape, const TailSolve& solve,
+                 int threads, size_t lds_bytes, hipStream_t st);
 
 }  // namespace chhs

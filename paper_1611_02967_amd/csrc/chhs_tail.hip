@@ -212,8 +212,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
                                                        const InstInfo* __restrict__ info,
                                                        const int* __restrict__ insts,
                                                        const int* __restrict__ active,
-                                                       unsigned cur_mask, CycleShape shape,
-                                                       double* pend) {
+                                                       unsigned cur_mask, CycleShape shape) {
     extern __shared__ __align__(16) unsigned char tail_lds[];
     T* base = reinterpret_cast<T*>(tail_lds);
     const int inst = insts[blockIdx.x];
@@ -232,10 +231,6 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
         const T* g0 = top > 0 ? G.fr0 : G.f0;
         const T* g1 = top > 0 ? G.fr1 : G.f1;
         const T* g2 = top > 0 ? G.fr2 : G.f2;
-        // a deferred shift of the finest p: subtracted here when the tail
-        // holds the finest level, then cleared (the finest level's first
-        // smoothing launch has already subtracted it otherwise)
-        const T psh = pend != nullptr && top == 0 ? T(pend[inst * kResStride + 4]) : T(0);
         // Every global load of the first rounds is issued before any LDS
         // store, so the staging waits for memory once: two cells of the top
         // level per thread (the LDS budget keeps the top below 2 kTailThreads
@@ -273,7 +268,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
             if (idx < G.n) {
                 S.phi[idx] = tv[k][0];
                 S.mu[idx] = tv[k][1];
-                S.p[idx] = tv[k][2] - psh;
+                S.p[idx] = tv[k][2];
                 S.f0[idx] = tv[k][3];
                 S.f1[idx] = tv[k][4];
                 S.f2[idx] = tv[k][5];
@@ -294,7 +289,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
         for (int idx = t0 + 2 * kTailThreads; idx < G.n; idx += blockDim.x) {
             S.phi[idx] = G.phi[idx];
             S.mu[idx] = G.mu[idx];
-            S.p[idx] = G.p[idx] - psh;
+            S.p[idx] = G.p[idx];
             S.f0[idx] = g0[idx];
             S.f1[idx] = g1[idx];
             S.f2[idx] = g2[idx];
@@ -312,7 +307,6 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
         }
     }
     __syncthreads();
-    if (pend != nullptr && threadIdx.x == 0) pend[inst * kResStride + 4] = 0.0;
     if (top > 0) {
         const Level<T> S = lds_view<T, CORR>(d, top, top, base);
         const float rnx = 1.0f / float(S.nx), rnxy = 1.0f / float(S.nx * S.ny);
@@ -409,23 +403,23 @@ int prepare_tail(int dim, size_t lds_bytes) {
 template <typename T, bool CORR>
 void launch_tail(int dim, const LevelDesc<T>* desc, const InstInfo* info, const int* insts,
                  int ninst, const int* active, unsigned cur_mask, const CycleShape& shape,
-                 double* pend, size_t lds_bytes, hipStream_t st) {
+                 size_t lds_bytes, hipStream_t st) {
     if (ninst <= 0) return;
     if (dim == 2)
         hipLaunchKernelGGL((k_tail<2, T, CORR>), dim3(ninst), dim3(kTailThreads), lds_bytes, st,
-                           desc, info, insts, active, cur_mask, shape, pend);
+                           desc, info, insts, active, cur_mask, shape);
     else
         hipLaunchKernelGGL((k_tail<3, T, CORR>), dim3(ninst), dim3(kTailThreads), lds_bytes, st,
-                           desc, info, insts, active, cur_mask, shape, pend);
+                           desc, info, insts, active, cur_mask, shape);
 }
 
 template int prepare_tail<double, false>(int, size_t);
 template int prepare_tail<float, true>(int, size_t);
 template void launch_tail<double, false>(int, const LevelDesc<double>*, const InstInfo*,
                                          const int*, int, const int*, unsigned,
-                                         const CycleShape&, double*, size_t, hipStream_t);
+                                         const CycleShape&, size_t, hipStream_t);
 template void launch_tail<float, true>(int, const LevelDesc<float>*, const InstInfo*, const int*,
-                                       int, const int*, unsigned, const CycleShape&, double*,
-                                       size_t, hipStream_t);
+                                       int, const int*, unsigned, const CycleShape&, size_t,
+                                       hipStream_t);
 
 }  // namespace chhs

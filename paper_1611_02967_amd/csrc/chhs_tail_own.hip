@@ -4,7 +4,9 @@
 // One workgroup per instance runs every level from the instance's tail level
 // down to the coarsest grid: smoothing, residual + restriction, FAS coarse
 // right-hand side, the coarsest-grid smoothing steps, prolongation +
-// correction.
+// correction.  Where the finest level itself is here (FP64), the cycle ends with
+// the norm of its residual, and when that holds for every instance of the
+// context one launch runs the cycles of a whole step up to the tolerance.
 //
 // What bounds it is latency: the V-cycle over these levels is a chain of about
 // fifty dependent phases, each a few cells per lane.  So a phase is kept
@@ -203,6 +205,7 @@ __device__ __forceinline__ void apply_n(const Pair<DIM, T>& P, const T* V, const
                                         T (&n)[3]) {
     constexpr int K = Pair<DIM, T>::K;
     const T gam = opaque(q.gam);
+    const unsigned fl = opaque(P.fl);       // the words below are formed anew, not kept
     const T x = P.u[C][0], muc = P.u[C][1], pc = P.u[C][2];
     T smm = 0, sap = 0, sphi = 0, sp = 0, samu = 0;
     auto add = [&](T a, T xphi, T xmu, T xp) {
@@ -218,7 +221,7 @@ __device__ __forceinline__ void apply_n(const Pair<DIM, T>& P, const T* V, const
     const T op = P.mid() ? P.u[1 - C][2] : pc;
     if constexpr (CORR) {
         const bool r = P.right(C);
-        const T* v = V + (P.has(C, 0) ? P.nb[C][0] : P.w(C));
+        const T* v = V + (((fl >> (2 + C * K)) & 1u) ? P.nb[C][0] : P.w(C));
         const T xphi = v[0], xmu = v[1], xp = v[2];
         add(r ? P.amid : P.a[C][0], r ? ophi : xphi, r ? omu : xmu, r ? op : xp);
         add(r ? P.a[C][0] : P.amid, r ? xphi : ophi, r ? xmu : omu, r ? xp : op);
@@ -227,7 +230,7 @@ __device__ __forceinline__ void apply_n(const Pair<DIM, T>& P, const T* V, const
     }
 #pragma unroll
     for (int k = CORR ? 1 : 0; k < K; ++k) {
-        const T* r = V + (P.has(C, k) ? P.nb[C][k] : P.w(C));
+        const T* r = V + (((fl >> (2 + C * K + k)) & 1u) ? P.nb[C][k] : P.w(C));
         add(P.a[C][k], r[0], r[1], r[2]);
     }
     if constexpr (CORR) {
@@ -242,12 +245,32 @@ __device__ __forceinline__ void apply_n(const Pair<DIM, T>& P, const T* V, const
     }
 }
 
+// An instance's results and flags, also into the host's mirror (fresh: new
+// results o, else those it has).
+__device__ __forceinline__ void write_results(const TailSolve& q, int inst, bool fresh,
+                                              const double* o, int act, int cycles) {
+    double* r = q.out.res + inst * kResStride;
+    double* m = q.out.mirror + inst * kResStride;
+    int* flags = reinterpret_cast<int*>(q.out.mirror + size_t(gridDim.x) * kResStride);
+    for (int k = 0; k < 6; ++k) {
+        if (fresh) r[k] = o[k];
+        m[k] = fresh ? o[k] : r[k];
+    }
+    if (fresh) {
+        q.out.act[inst] = act;
+        q.out.cycles[inst] = cycles;
+    }
+    flags[inst] = fresh ? act : 0;
+    flags[gridDim.x + inst] = fresh ? cycles : q.out.cycles[inst];
+}
+
 template <int DIM, typename T, bool CORR, int NT>
 __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__ tails,
                                              const TailOwner* __restrict__ owners, int stride,
                                              const int* __restrict__ active, CycleShape shape,
-                                             double* pend) {
+                                             TailSolve solve) {
     extern __shared__ __align__(16) unsigned char own_lds[];
+    __shared__ double sums[2][NT / 64][4];      // two, so that a slow wave may still read the last
     T* const base = reinterpret_cast<T*>(own_lds);
     constexpr int K = Pair<DIM, T>::K;
     const int inst = blockIdx.x, tid = threadIdx.x;
@@ -256,7 +279,10 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
     // away from the launch
     const TailOwner own = owners[inst * stride + tid];
     const TailDesc<T>& G = tails[inst];
-    if (active != nullptr && active[inst] == 0) return;
+    if (active != nullptr && active[inst] == 0) {
+        if (solve.cycles > 0 && tid == 0) write_results(solve, inst, false, nullptr, 0, 0);
+        return;
+    }
     if (G.levels == 0) return;          // the instance's tail is worked by k_tail
     const bool owner = (own.fl >> kOwnValid) & 1u;
     const int my = owner ? int((own.fl >> kOwnLevel) & 7u) : -1;       // level below the tail's top one
@@ -280,11 +306,6 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
     T* const B = PS + n;                // correction form
     const int e0 = (own.fl >> kOwnRed) & 1u;    // the red member
     const int par = own.par;
-
-    // A deferred shift of the finest p: subtracted here when the tail holds the
-    // finest level, then cleared (the finest level's first smoothing launch
-    // has already subtracted it otherwise).
-    const T psh = pend != nullptr && finest ? T(pend[inst * kResStride + 4]) : T(0);
 
     Pair<DIM, T> P;
     P.fl = own.fl;
@@ -325,7 +346,7 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
             if (my == 0 && live) {
                 P.u[c][0] = g[c][0];
                 P.u[c][1] = g[c][1];
-                P.u[c][2] = g[c][2] - psh;
+                P.u[c][2] = g[c][2];
                 P.f[c][0] = g[c][3];
                 P.f[c][1] = g[c][4];
                 P.f[c][2] = CORR ? g[c][5] : g[c][5] * cf.inv_lam;
@@ -337,7 +358,6 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
         }
     }
     __syncthreads();
-    if (pend != nullptr && tid == 0) pend[inst * kResStride + 4] = 0.0;
     if (owner) {
         // face coefficients of the pair
         P.amid = P.mid() ? T(0.5) * (ps[0] + ps[1]) : T(0);
@@ -417,98 +437,155 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
         sync(is(single, 0));
     }
 
-    for (int l = 0; l <= last; ++l) {
-        if (l > 0 && my == l) {
-            // the restricted iterate and f = fr + N(u); the neighbours' values
-            // come from UB, which the first phase does not overwrite (the record
-            // of a missing second member is not used)
+    for (int cycle = 1;; ++cycle) {
+        // nothing derived from these is kept over the whole loop (registers)
+        P.cell0 = opaque(P.cell0);
+        P.fl = opaque(P.fl);
+        cf.lam = opaque(cf.lam);
+        cf.kap = opaque(cf.kap);
+        for (int l = 0; l <= last; ++l) {
+            if (l > 0 && my == l) {
+                // the restricted iterate and f = fr + N(u); the neighbours' values
+                // come from UB, which the first phase does not overwrite (the record
+                // of a missing second member is not used)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const bool live = P.alive(c);
-                const int w = live ? P.w(c) : 0;
-                T v[7];
-                for (int k = 0; k < 3; ++k) v[k] = UB[w + k];
-                for (int k = 0; k < 3; ++k) v[3 + k] = FR[w + k];
-                if (CORR) v[6] = B[live ? P.cell(c) : 0];
-                for (int k = 0; k < 3; ++k) P.u[c][k] = live ? v[k] : T(0);
-                P.f[c][0] = live ? v[3] : T(0);
-                P.f[c][1] = live ? v[4] : T(0);
-                P.f[c][2] = live ? (CORR ? v[5] : v[5] * cf.inv_lam) : T(0);
-                if (CORR) P.d0[c] = live ? v[6] : T(0);
-            }
-            T n0[3], n1[3];
-            apply_n<DIM, T, CORR, 0>(P, UB, cf, n0);
-            apply_n<DIM, T, CORR, 1>(P, UB, cf, n1);
+                for (int c = 0; c < 2; ++c) {
+                    const bool live = P.alive(c);
+                    const int w = live ? P.w(c) : 0;
+                    T v[7];
+                    for (int k = 0; k < 3; ++k) v[k] = UB[w + k];
+                    for (int k = 0; k < 3; ++k) v[3 + k] = FR[w + k];
+                    if (CORR) v[6] = B[live ? P.cell(c) : 0];
+                    for (int k = 0; k < 3; ++k) P.u[c][k] = live ? v[k] : T(0);
+                    P.f[c][0] = live ? v[3] : T(0);
+                    P.f[c][1] = live ? v[4] : T(0);
+                    P.f[c][2] = live ? (CORR ? v[5] : v[5] * cf.inv_lam) : T(0);
+                    if (CORR) P.d0[c] = live ? v[6] : T(0);
+                }
+                T n0[3], n1[3];
+                apply_n<DIM, T, CORR, 0>(P, UB, cf, n0);
+                apply_n<DIM, T, CORR, 1>(P, UB, cf, n1);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                P.f[0][k] += n0[k];
-                P.f[1][k] += n1[k];
-            }
-        }
-        smooth(l, l == last ? shape.coarse : (l == 0 ? nu1 : shape.nu1c));
-        if (l == last) break;
-        if (my == l) {
-            // residual of the pair, restricted by cell averaging with the other
-            // pairs of the coarse cell (lanes of one group of 2 or 4)
-            T n0[3], n1[3], v[7];
-            apply_n<DIM, T, CORR, 0>(P, U, cf, n0);
-            apply_n<DIM, T, CORR, 1>(P, U, cf, n1);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                v[k] = (P.f[0][k] - n0[k]) + (P.f[1][k] - n1[k]);
-                v[3 + k] = P.u[0][k] + P.u[1][k];
-            }
-            if (!CORR) v[2] *= cf.lam;
-            v[6] = P.d0[0] + P.d0[1];           // b
-            const T wgt = DIM == 3 ? T(0.125) : T(0.25);
-#pragma unroll
-            for (int k = 0; k < 7; ++k) {
-                if (!CORR && k == 6) continue;
-                v[k] += quad<kLane1>(v[k]);
-                if (DIM == 3) v[k] += quad<kLane2>(v[k]);
-                v[k] *= wgt;
-            }
-            const int cn = n >> DIM;
-            T* const CU = U + own_words(n, CORR);
-            T* const CUB = CU + 3 * (cn + 1);
-            T* const CFR = CUB + 3 * cn;
-            if ((own.fl >> kOwnFirst) & 1u) {
                 for (int k = 0; k < 3; ++k) {
-                    CU[3 * par + k] = v[3 + k];
-                    CUB[3 * par + k] = v[3 + k];
-                    CFR[3 * par + k] = v[k];
+                    P.f[0][k] += n0[k];
+                    P.f[1][k] += n1[k];
                 }
-                if (CORR) CFR[4 * cn + par] = v[6];
             }
-        }
-        sync(is(joined, l));
-    }
-
-    for (int l = last - 1; l >= 0; --l) {
-        // a coarser level of one wave other than this level's
-        if (is(single, l + 1) && !is(joined, l)) __syncthreads();
-        if (my == l) {
-            const int cn = n >> DIM;
-            const T* const CU = U + own_words(n, CORR);
-            const T* const CUB = CU + 3 * (cn + 1);
+            smooth(l, l == last ? shape.coarse : (l == 0 ? nu1 : shape.nu1c));
+            if (l == last) break;
+            if (my == l) {
+                // residual of the pair, restricted by cell averaging with the other
+                // pairs of the coarse cell (lanes of one group of 2 or 4)
+                T n0[3], n1[3], v[7];
+                apply_n<DIM, T, CORR, 0>(P, U, cf, n0);
+                apply_n<DIM, T, CORR, 1>(P, U, cf, n1);
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                if (shape.bilinear != 0) {
-                    const int* g = &owners[inst * stride + tid].nx;     // nx, nx ny
-                    const int fx = g[0], fxy = g[1];
-                    int i, j, k;
-                    decode<DIM>(P.cell(c), fx, fxy / fx, i, j, k);
-                    for (int m = 0; m < 3; ++m)
-                        P.u[c][m] += bilinear_corr<DIM, T, 3>(CU + m, CUB + m, fx >> 1,
-                                                              (fxy / fx) >> 1, (n / fxy) >> 1, i, j, k);
-                } else {
-                    for (int m = 0; m < 3; ++m) P.u[c][m] += CU[3 * par + m] - CUB[3 * par + m];
+                for (int k = 0; k < 3; ++k) {
+                    v[k] = (P.f[0][k] - n0[k]) + (P.f[1][k] - n1[k]);
+                    v[3 + k] = P.u[0][k] + P.u[1][k];
                 }
-                for (int m = 0; m < 3; ++m) U[P.w(c) + m] = P.u[c][m];
+                if (!CORR) v[2] *= cf.lam;
+                v[6] = P.d0[0] + P.d0[1];           // b
+                const T wgt = DIM == 3 ? T(0.125) : T(0.25);
+#pragma unroll
+                for (int k = 0; k < 7; ++k) {
+                    if (!CORR && k == 6) continue;
+                    v[k] += quad<kLane1>(v[k]);
+                    if (DIM == 3) v[k] += quad<kLane2>(v[k]);
+                    v[k] *= wgt;
+                }
+                const int cn = n >> DIM;
+                T* const CU = U + own_words(n, CORR);
+                T* const CUB = CU + 3 * (cn + 1);
+                T* const CFR = CUB + 3 * cn;
+                if ((own.fl >> kOwnFirst) & 1u) {
+                    for (int k = 0; k < 3; ++k) {
+                        CU[3 * par + k] = v[3 + k];
+                        CUB[3 * par + k] = v[3 + k];
+                        CFR[3 * par + k] = v[k];
+                    }
+                    if (CORR) CFR[4 * cn + par] = v[6];
+                }
             }
+            sync(is(joined, l));
         }
-        sync(is(single, l));
-        smooth(l, l == 0 ? nu2 : shape.nu2c);
+
+        for (int l = last - 1; l >= 0; --l) {
+            // a coarser level of one wave other than this level's
+            if (is(single, l + 1) && !is(joined, l)) __syncthreads();
+            if (my == l) {
+                const int cn = n >> DIM;
+                const T* const CU = U + own_words(n, CORR);
+                const T* const CUB = CU + 3 * (cn + 1);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    if (shape.bilinear != 0) {
+                        const int* g = &owners[inst * stride + tid].nx;     // nx, nx ny
+                        const int fx = g[0], fxy = g[1];
+                        int i, j, k;
+                        decode<DIM>(P.cell(c), fx, fxy / fx, i, j, k);
+                        for (int m = 0; m < 3; ++m)
+                            P.u[c][m] += bilinear_corr<DIM, T, 3>(CU + m, CUB + m, fx >> 1,
+                                                                  (fxy / fx) >> 1, (n / fxy) >> 1, i, j, k);
+                    } else {
+                        for (int m = 0; m < 3; ++m) P.u[c][m] += CU[3 * par + m] - CUB[3 * par + m];
+                    }
+                    for (int m = 0; m < 3; ++m) U[P.w(c) + m] = P.u[c][m];
+                }
+            }
+            sync(is(single, l));
+            smooth(l, l == 0 ? nu2 : shape.nu2c);
+        }
+
+        // The finest level is here (FP64): the norm of its residual.  Sums over
+        // each wave of its owners, then over the waves, in a fixed order.
+        if constexpr (CORR) {
+            break;
+        } else {
+            if (!finest || solve.partial == nullptr) break;
+            if (my == 0) {
+                T n[3];
+                apply_n<DIM, T, CORR, 0>(P, U, cf, n);
+                double v[4] = {0.0, 0.0, 0.0, P.u[0][2] + P.u[1][2]};
+                auto add = [&](int c) {
+                    for (int k = 0; k < 3; ++k) {
+                        const T r = (k == 2 ? cf.lam : T(1)) * (P.f[c][k] - n[k]);
+                        v[k] += r * r;
+                    }
+                };
+                add(0);
+                __builtin_amdgcn_sched_barrier(0);      // one member at a time (registers)
+                apply_n<DIM, T, CORR, 1>(P, U, cf, n);
+                add(1);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+                    if ((tid & 63) == 0) sums[cycle & 1][tid >> 6][k] = v[k];
+                }
+            }
+            __syncthreads();
+            double t[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int w = 0; w < G.top_waves; ++w)
+                for (int k = 0; k < 4; ++k) t[k] += sums[cycle & 1][w][k];
+            if (solve.cycles == 0) {
+                // one cycle: the partial for the reduction that ends it
+                if (tid == 0)
+                    for (int k = 0; k < 4; ++k)
+                        gstore(solve.partial, G.part * kNormStride + k, t[k]);
+                break;
+            }
+            // cycles up to the tolerance: the stopping test of k_inst_reduce
+            const InstInfo& in = solve.info[inst];
+            const double hd = in.dim == 3 ? in.h * in.h * in.h : in.h * in.h;
+            const double tot = sqrt((t[0] + t[1] + t[2]) * hd);
+            if (tot > solve.tol && tot < 1e300 && cycle < solve.cycles) continue;
+            if (tid == 0) {
+                const double o[6] = {sqrt(t[0] * hd), sqrt(t[1] * hd), sqrt(t[2] * hd), tot,
+                                     t[3] / double(in.n0), tot < 1e300 ? 0.0 : 1.0};
+                write_results(solve, inst, true, o, 0, cycle);
+            }
+            break;
+        }
     }
 
     if (my == 0)
@@ -529,7 +606,7 @@ template <typename T, bool CORR>
 auto own_kernel(int dim, int threads) {
     if constexpr (CORR) {
         if (threads <= 512) return dim == 2 ? &k_tail_own<2, T, CORR, 512> : &k_tail_own<3, T, CORR, 512>;
-        return dim == 2 ? &k_tail_own<2, T, CORR, 1024> : &k_tail_own<3, T, CORR, 768>;
+        return dim == 2 ? &k_tail_own<2, T, CORR, 1024> : &k_tail_own<3, T, CORR, 1024>;
     } else {
         if (dim == 3) return &k_tail_own<3, T, CORR, 512>;
         return threads <= 512 ? &k_tail_own<2, T, CORR, 512> : &k_tail_own<2, T, CORR, 768>;
@@ -548,20 +625,20 @@ int prepare_tail_own(int dim, int threads, size_t lds_bytes) {
 
 template <typename T, bool CORR>
 void launch_tail_own(int dim, const TailDesc<T>* tails, const TailOwner* owners, int ninst,
-                 const int* active, const CycleShape& shape, double* pend, int threads,
-                 size_t lds_bytes, hipStream_t st) {
+                 const int* active, const CycleShape& shape, const TailSolve& solve,
+                 int threads, size_t lds_bytes, hipStream_t st) {
     if (ninst <= 0) return;
     hipLaunchKernelGGL((own_kernel<T, CORR>(dim, threads)), dim3(ninst), dim3(threads), lds_bytes,
-                       st, tails, owners, threads, active, shape, pend);
+                       st, tails, owners, threads, active, shape, solve);
 }
 
 template int prepare_tail_own<double, false>(int, int, size_t);
 template int prepare_tail_own<float, true>(int, int, size_t);
 template void launch_tail_own<double, false>(int, const TailDesc<double>*, const TailOwner*, int,
-                                         const int*, const CycleShape&, double*, int, size_t,
-                                         hipStream_t);
+                                         const int*, const CycleShape&, const TailSolve&, int,
+                                     size_t, hipStream_t);
 template void launch_tail_own<float, true>(int, const TailDesc<float>*, const TailOwner*, int,
-                                       const int*, const CycleShape&, double*, int, size_t,
-                                       hipStream_t);
+                                       const int*, const CycleShape&, const TailSolve&, int,
+                                     size_t, hipStream_t);
 
 }  // namespace chhs

@@ -72,3 +72,44 @@ def test_mixed_step_matches_oracle(chhs, shape):
     ref = fas.solve_step(prev, cur, mu0, p0 - p0.mean(), prm, fas.Opts(tol=1e-10))
     assert np.max(np.abs(t[1].cpu().numpy() - ref.phi)) <= 1e-8
     assert np.max(np.abs(t[2].cpu().numpy() - ref.mu)) <= 1e-8
+
+
+# every instance's finest level in the tail: the cycles of a step are one launch
+@pytest.mark.parametrize("shapes", [[(16, 16)], [(32, 32), (4, 4), (14, 10)], [(8, 8, 8), (4, 4, 4)]],
+                         ids=["16", "ragged", "3d"])
+def test_steps_held_by_the_tail_match_cycle_launches_and_oracle(chhs, shapes):
+    import torch
+    prms = [scheme.Params(eps=0.1, gamma=2.0, s=1e-3, h=1.0 / sh[-1]) for sh in shapes]
+    ins = [_inputs(sh, 8300 + 10 * i) for i, sh in enumerate(shapes)]
+    probs = [chhs.make_problem(sh, q.h, q.eps, q.gamma, q.s) for sh, q in zip(shapes, prms)]
+
+    def state():
+        return [torch.cat([dev(v[k].reshape(-1)) for v in ins]) for k in range(4)]
+    one, many = state(), state()
+    _, a = chhs.Solver(probs, chhs.chhs_default_opts()).step(*one, 2)
+    # a context that times its kernels launches every cycle
+    _, b = chhs.Solver(probs, chhs.chhs_default_opts(timing=1)).step(*many, 2)
+    for x, y in zip(one, many):
+        assert torch.equal(x, y)
+    assert [(s["vcycles"], s["total_vcycles"]) for s in a] == [(s["vcycles"], s["total_vcycles"])
+                                                               for s in b]
+    at = 0
+    for sh, prm, (prev, cur, mu, p) in zip(shapes, prms, ins):
+        for _ in range(2):
+            r = fas.solve_step(prev, cur, mu, p - p.mean(), prm, fas.Opts(tol=1e-10))
+            prev, cur, mu, p = cur, r.phi, r.mu, r.p
+        got = one[1][at:at + cur.size].cpu().numpy().reshape(sh)
+        assert np.max(np.abs(got - cur)) <= 1e-9
+        at += cur.size
+
+
+def test_step_held_by_the_tail_stops_at_max_vcycles(chhs):
+    sh = (16, 16)
+    sv = chhs.Solver(chhs.make_problem(sh, 1.0 / 16, 0.1, 2.0, 1e-3),
+                     chhs.chhs_default_opts(max_vcycles=2))
+    t = [dev(v) for v in _inputs(sh, 8400)]
+    before = [v.clone() for v in t]
+    rc, st = sv.step(*t, 1, check=False)
+    assert rc == chhs.CHHS_E_NOCONV and st[0]["vcycles"] == 2 and st[0]["res_norm"] > 1e-10
+    for x, y in zip(t, before):
+        assert bool((x == y).all())
