@@ -287,7 +287,7 @@ int chhs_level_shape(chhs_ctx* c, int32_t level, int32_t* nxyz3);
 int chhs_level_kernel(chhs_ctx* c, int32_t level, int32_t* out3);
 int chhs_copy_field(chhs_ctx* c, int32_t level, int32_t field, double* dev, int32_t dir);
 
-/* How the counted cycles run: *graphs = the number of cycle graphs captured
+/* How the counted cycles run: *graphs = the number of graphs of one cycle captured
  * and instantiated so far (0 before the first step, 2 for the plain FP64
  * loop, 1 or 2 for mixed precision), 0 when they launch directly
  * (use_graph = 0, timing != 0, or a capture that failed, which disables

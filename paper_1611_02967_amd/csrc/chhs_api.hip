@@ -217,6 +217,11 @@ struct chhs_ctx {
     // level alternates its copy once per refinement step)
     hipGraph_t graph[2] = {nullptr, nullptr};
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
+    // graphs of several cycles, captured when a step first wants them (at most
+    // one per kCycleRuns entry, copy of the mixed finest level and mirror)
+    struct Run { int cycles, copy, mirror; hipGraph_t graph; hipGraphExec_t exec; };
+    std::vector<Run> runs;
+    int last_cycles = 0;            // cycles of the last step (the slowest instance's)
     bool graph_failed = false;
     int capturing = -1;             // slot being captured, -1 when none
     // kernel timing (opts.timing)
@@ -1774,6 +1779,40 @@ void drop_graphs(chhs_ctx* c) {
         }
         c->graph_pairs[s].clear();
     }
+    for (auto& r : c->runs) {
+        (void)hipGraphExecDestroy(r.exec);
+        (void)hipGraphDestroy(r.graph);
+    }
+    c->runs.clear();
+}
+
+// Cycles that may be replayed as one graph.  The device waits about 13 us from
+// the end of one graph to the start of the next (its kernels follow each other
+// without a gap), of 45 us a cycle at 64^2 and 120 us at 512^2.
+constexpr int kCycleRuns[] = {16, 12, 8, 6, 4, 3, 2};
+
+// The graph of n counted cycles from the current copy, results to mirror buf;
+// null when it cannot be captured (the caller then replays single cycles).
+hipGraphExec_t cycle_run(chhs_ctx* c, int n, int buf) {
+    const int copy = c->mixed ? c->cur[0] : 0;
+    for (const auto& r : c->runs)
+        if (r.cycles == n && r.copy == copy && r.mirror == buf) return r.exec;
+    chhs_ctx::Run r{n, copy, buf, nullptr, nullptr};
+    const int saved_cur0 = c->cur[0];
+    bool ok = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess;
+    if (ok) {
+        for (int k = 0; k < n; ++k) enqueue_cycle(c, true, buf);
+        ok = hipStreamEndCapture(c->stream, &r.graph) == hipSuccess && r.graph != nullptr;
+    }
+    c->cur[0] = saved_cur0;   // the capture did not run anything
+    if (ok && hipGraphInstantiate(&r.exec, r.graph, nullptr, nullptr, 0) != hipSuccess) ok = false;
+    (void)hipGetLastError();
+    if (!ok) {
+        if (r.graph) (void)hipGraphDestroy(r.graph);
+        return nullptr;
+    }
+    c->runs.push_back(r);
+    return r.exec;
 }
 
 // Captures the counted cycle into graph slot `slot` (reading back into mirror
@@ -1848,7 +1887,10 @@ bool expect_more(const chhs_ctx* c, const std::vector<double>& rho) {
 // and mirrors as plain cycles do.
 // setup_pending: the step's setup was enqueued without waiting, its norms
 // arriving in the third mirror; the first cycle is then enqueued at once (it
-// does nothing for an instance that is converged already).
+// does nothing for an instance that is converged already).  The first launch of
+// such a step replays as many cycles as the last step needed, less one, as one
+// graph (cycles of converged instances do nothing, so the count of the last
+// step is a schedule and nothing else).
 int run_cycles(chhs_ctx* c, bool setup_pending = false) {
     if (!setup_pending && !any_active(c)) return CHHS_OK;
     for (int s = 0; s < 2; ++s)
@@ -1867,38 +1909,60 @@ int run_cycles(chhs_ctx* c, bool setup_pending = false) {
     std::vector<double> prev(c->n_inst, 0.0), rho(c->n_inst, 0.1);
     if (!setup_pending)
         for (int i = 0; i < c->n_inst; ++i) prev[i] = c->hres[size_t(i) * chhs::kResStride + 3];
-    size_t mark[2] = {0, 0};       // pending timing pairs before each mirror's latest cycle
-    int queue[2], nq = 0, next = c->mixed ? c->cur[0] : 0;
-    auto launch = [&]() -> int {
-        const int s = next;
-        mark[s] = c->pending.size();
-        if (graphs) {
-            HIP_TRY(hipGraphLaunch(c->gexec[s], c->stream));
-            if (c->mixed) c->cur[0] ^= 1;    // as the captured step does
+    struct Flight {
+        int mirror, event, cycles;
+        size_t mark;               // pending timing pairs before it
+    };
+    Flight queue[2];
+    int nq = 0, next = c->mixed ? c->cur[0] : 0, launches = 0;
+    // n cycles (n > 1: one graph, where it can be captured)
+    auto launch = [&](int n) -> int {
+        Flight f{next, launches++ & 1, 1, c->pending.size()};
+        hipGraphExec_t run = nullptr;
+        if (graphs && n > 1) {
+            // a mixed single step reads back into the mirror of the copy it
+            // starts from: this run takes the other one than its successor
+            if (c->mixed) f.mirror = (c->cur[0] ^ (n & 1)) ^ 1;
+            run = cycle_run(c, n, f.mirror);
+            if (run == nullptr) f.mirror = next;
+        }
+        if (run != nullptr) {
+            HIP_TRY(hipGraphLaunch(run, c->stream));
+            if (c->mixed) c->cur[0] ^= n & 1;    // as the captured steps do
+            f.cycles = n;
+        } else if (graphs) {
+            HIP_TRY(hipGraphLaunch(c->gexec[f.mirror], c->stream));
+            if (c->mixed) c->cur[0] ^= 1;
         } else {
-            enqueue_cycle(c, true, s);
+            enqueue_cycle(c, true, f.mirror);
             const int rc = check_launch();
             if (rc) return rc;
         }
-        HIP_TRY(hipEventRecord(c->cycle_done[s], c->stream));
-        queue[nq++] = s;
-        next ^= 1;
+        HIP_TRY(hipEventRecord(c->cycle_done[f.event], c->stream));
+        queue[nq++] = f;
+        next = f.mirror ^ 1;
         return CHHS_OK;
     };
-    int rc = launch();
+    // all but the last of the cycles that the last step took, in one graph
+    int first = 1;
+    if (setup_pending && graphs && !whole_in_tail(c))
+        for (int n : kCycleRuns)
+            if (n <= c->last_cycles - 1) {
+                first = n;
+                break;
+            }
+    int rc = launch(first);
     if (rc) return rc;
     for (;;) {
         if (nq == 1 && !whole_in_tail(c) && (setup_pending || expect_more(c, rho))) {
-            rc = launch();
+            rc = launch(1);
             if (rc) return rc;
         }
-        const int s = queue[0];
+        const Flight f = queue[0];
         queue[0] = queue[1];
         --nq;
-        HIP_TRY(hipEventSynchronize(c->cycle_done[s]));
-        if (graphs)
-            for (auto& pe : c->graph_pairs[s]) accumulate(c, pe);
-        view_results(c, s);
+        HIP_TRY(hipEventSynchronize(c->cycle_done[f.event]));
+        view_results(c, f.mirror);
         if (setup_pending) {
             // the setup ran before this cycle: its norms are on the host now
             for (int i = 0; i < c->n_inst; ++i) prev[i] = c->hbuf[2][size_t(i) * chhs::kResStride + 3];
@@ -1906,27 +1970,30 @@ int run_cycles(chhs_ctx* c, bool setup_pending = false) {
         }
         for (int i = 0; i < c->n_inst; ++i) {
             const double r = c->hres[size_t(i) * chhs::kResStride + 3];
-            if (prev[i] > 0.0 && std::isfinite(r)) rho[i] = r / prev[i];
+            if (prev[i] > 0.0 && std::isfinite(r))
+                rho[i] = f.cycles == 1 ? r / prev[i] : std::pow(r / prev[i], 1.0 / f.cycles);
             prev[i] = r;
         }
         if (!any_active(c)) {
             if (nq == 1) {
                 // enqueued before this result: it runs with no active instance
-                const int d = queue[0];
-                HIP_TRY(hipEventSynchronize(c->cycle_done[d]));
-                for (size_t i = mark[d]; i < c->pending.size(); ++i) {
+                const Flight d = queue[0];
+                HIP_TRY(hipEventSynchronize(c->cycle_done[d.event]));
+                for (size_t i = d.mark; i < c->pending.size(); ++i) {
                     c->ev_pool.push_back(c->pending[i].a);
                     c->ev_pool.push_back(c->pending[i].b);
                 }
-                c->pending.resize(mark[d]);
+                c->pending.resize(d.mark);
             }
             break;
         }
         if (nq == 0) {
-            rc = launch();
+            rc = launch(1);
             if (rc) return rc;
         }
     }
+    c->last_cycles = 0;
+    for (int i = 0; i < c->n_inst; ++i) c->last_cycles = std::max(c->last_cycles, c->hcyc[i]);
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->last_slot = -1;
     resolve_timing(c);
