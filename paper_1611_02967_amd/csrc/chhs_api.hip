@@ -18,6 +18,7 @@
 #include "chhs_internal.hpp"
 
 using chhs::Batch;
+using chhs::BrickTask;
 using chhs::CellTask;
 using chhs::FoldTask;
 using chhs::InstInfo;
@@ -89,6 +90,9 @@ struct Layout {
     int zseg64[kMaxLevels] = {}, zseg32[kMaxLevels] = {};
     // 3D level smoothed by the fused step (else by one launch per color)
     bool z3[kMaxLevels] = {};
+    // 3D FP64 level smoothed in bricks: steps per launch (0: not); its bricks
+    int brick[kMaxLevels] = {};
+    std::vector<std::vector<BrickTask>> K;
     bool strip[kMaxLevels] = {};            // level smoothed by the row-streaming kernel
     int tile_threads[kMaxLevels] = {};      // tiles: threads per block, 0 = by the tile count
     int tile_threads_post[kMaxLevels] = {}; // ... of the post-smoothing launches (0 = the same)
@@ -141,7 +145,7 @@ struct Layout {
     size_t off_FA0 = 0, off_FA0n = 0, off_rngA0f = 0, off_rngA0nf = 0, off_partial_f = 0;
     size_t off_partial = 0, off_res = 0, off_act = 0, off_cycles = 0, off_act_last = 0;
     std::vector<size_t> off_A, off_B, off_Bc, off_Bh, off_Bcs, off_T, off_Tall, off_S, off_Sall,
-        off_Z64, off_Z32, off_ZR64, off_ZR32, off_BcS;
+        off_Z64, off_Z32, off_ZR64, off_ZR32, off_BcS, off_K;
     int partial_cap = 0, partial_t_cap = 0;
 };
 
@@ -167,6 +171,7 @@ struct chhs_ctx {
     Table<StripTask> S[kMaxLevels], Sall[kMaxLevels];
     Table<Step3Task> Z64[kMaxLevels], Z32[kMaxLevels], ZR64[kMaxLevels], ZR32[kMaxLevels];
     Table<CellTask> BcS[kMaxLevels];
+    Table<BrickTask> K[kMaxLevels];
     Table<CellTask> A0n, A0t, A0x;
     Range* rngA0x = nullptr;
     Table<StripTask> M0;
@@ -546,6 +551,8 @@ void level0_ranges(Layout& L, int n_inst) {
                 at += n;
             }
     }
+    else if (L.brick[0] > 0)
+        task_ranges(L.rngT0, n_inst, L.K[0]);
     else
         task_ranges(L.rngT0, n_inst, L.Z64[0]);     // 3D
 }
@@ -607,6 +614,41 @@ int step3_seg(const std::vector<int>& nxs, const std::vector<int>& nys, const st
     return 8;
 }
 
+// Bricks of one FP64 3D level over the listed instances (extents, -1 = skip) and
+// the steps per launch, 0 for no bricks.  A finest level is in bricks if no
+// instance has more than kBrickFinest cells there (by instance, as the sums of
+// the norm and of p's mean follow the bricks and a batched instance keeps the
+// bits of its single run); a coarse level if the batch has at most kBrickCoarse
+// cells there (larger launches are bound by throughput, and the per-color ones,
+// which give the same bits, recompute nothing).  Two steps while the bricks of
+// two steps (one workgroup per compute unit, by their LDS) are all resident at
+// once.  Two steps of the scheme, per-color launches / bricks: 16^3 928 / 583
+// us, 32^3 1509 / 903, 48 x 32 x 64 2020 / 1253, 64^3 (coarse levels) 2442 /
+// 1886, 64 grids of 16^3 1306 / 1195; beyond: 80^3 with its finest level per
+// color 2675 us, in bricks 2843, 8 grids of 64^3 6187 and 6588.
+constexpr long kBrickFinest = 1L << 17, kBrickCoarse = 1L << 18;
+constexpr long kBrickTwo = 256;
+int brick_tasks(std::vector<BrickTask>& out, bool finest, const std::vector<int>& nxs,
+                const std::vector<int>& nys, const std::vector<int>& nzs) {
+    long total = 0;
+    for (size_t i = 0; i < nxs.size(); ++i) {
+        if (nxs[i] < 0) continue;
+        const long n = long(nxs[i]) * nys[i] * nzs[i];
+        total += n;
+        if (n > (finest ? kBrickFinest : kBrickCoarse)) return 0;
+    }
+    if (!finest && total > kBrickCoarse) return 0;
+    const int tx = chhs::kBrickX, ty = chhs::kBrickY, tz = chhs::kBrickZ;
+    for (size_t i = 0; i < nxs.size(); ++i) {
+        if (nxs[i] < 0) continue;
+        for (int bz = 0; bz < (nzs[i] + tz - 1) / tz; ++bz)
+            for (int by = 0; by < (nys[i] + ty - 1) / ty; ++by)
+                for (int bx = 0; bx < (nxs[i] + tx - 1) / tx; ++bx)
+                    out.push_back({int(i), bx, by, bz});
+    }
+    return out.empty() ? 0 : (long(out.size()) <= kBrickTwo ? 2 : 1);
+}
+
 // Rows per segment of the row-marching refinement tasks: the longest segment
 // (fewer halo rows read twice) that still gives at least kMarchWavesWanted
 // waves over the batch (enough resident waves to keep loads in flight), but
@@ -648,6 +690,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     L.S.resize(kMaxLevels);
     L.Sall.resize(kMaxLevels);
     L.Z64.resize(kMaxLevels);
+    L.K.resize(kMaxLevels);
     L.Z32.resize(kMaxLevels);
     L.ZR64.resize(kMaxLevels);
     L.ZR32.resize(kMaxLevels);
@@ -729,7 +772,8 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         const bool first = o->order == 1;
         in.order = first ? 1 : 2;
         // the finest level's norm partials: from the fused 2D post launch, or
-        // (3D) from the z-marching residual kernel over the fused-step tasks
+        // (3D) from the last brick launch or the z-marching residual kernel over
+        // the fused-step tasks
         // (the mixed 3D path: from the z-marching refinement step)
         // or, held by the tail with owner threads, from the tail itself
         in.fused = (!first && tail > 0 &&
@@ -884,6 +928,8 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
             // (the autotuner may choose anew)
             const int zs = mixed ? L.zseg32[l] : L.zseg64[l];
             L.z3[l] = o->smoother == 4 || zs >= kStep3MinSeg;
+            if (o->smoother == 0 && !mixed && !L.z3[l] && nu_pre(*o, l) > 0 && nu_post(*o, l) > 0)
+                L.brick[l] = brick_tasks(L.K[l], l == 0, lnx_t[l], lny[l], lnz[l]);
         }
     // 3D restriction per instance (never by what else the batch holds): the
     // z-marching residual kernel on levels of at least kRes3MinCells cells, the
@@ -931,7 +977,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     L.partial_cap = int(std::max(L.A[0].size(), L.M0.size()));
     L.partial_t_cap =
         L.tail_parts + int(std::max<size_t>(1, std::max({L.T[0].size(), L.cap_T[0], L.S[0].size(),
-                                                         L.cap_S[0], L.Z64[0].size()})));
+                                                         L.cap_S[0], L.Z64[0].size(), L.K[0].size()})));
     L.off_desc = take(L.desc.size() * sizeof(LevelDesc<double>));
     L.off_desc32 = take(std::max<size_t>(1, L.desc32.size()) * sizeof(LevelDesc<float>));
     L.off_info = take(L.info.size() * sizeof(InstInfo));
@@ -969,6 +1015,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         L.off_ZR64.push_back(take(L.ZR64[l].size() * sizeof(Step3Task)));
         L.off_ZR32.push_back(take(L.ZR32[l].size() * sizeof(Step3Task)));
         L.off_BcS.push_back(take(L.BcS[l].size() * sizeof(CellTask)));
+        L.off_K.push_back(take(L.K[l].size() * sizeof(BrickTask)));
     }
     L.off_partial = take(size_t(L.partial_cap) * chhs::kPartialStride * sizeof(double));
     L.off_partial_t = take(size_t(L.partial_t_cap) * chhs::kNormStride * sizeof(double));
@@ -1157,6 +1204,25 @@ void step3(chhs_ctx* c, const Hier<T>& H, int l, const int* active, int cls, int
     H.cur[l] ^= 1;
 }
 
+// Smoothing launches on a level in bricks: n steps on level l, `last` in the
+// last launch (epi of launch_brick3d), the prolongation, the right-hand side or
+// the pending mean of p in the first; flips the level's current copy.
+void bricks(chhs_ctx* c, const Hier<double>& H, int l, int n, int last, const int* active, int cls,
+            bool pro, bool rhs, const double* psh) {
+    for (bool first = true; n > 0; first = false) {
+        const int k = std::min(n, c->lay.brick[l]);
+        n -= k;
+        Batch<double> b = make_batch(H.dev, H.cur, l, active);
+        b.pshift = first ? psh : nullptr;
+        {
+            TimedScope t(c, cls);
+            chhs::launch_brick3d(b, c->K[l].dev, c->K[l].n, l == 0, k, n == 0 ? last : 0,
+                                 pro && first, rhs && first, level0_partials(c), c->stream);
+        }
+        H.cur[l] ^= 1;
+    }
+}
+
 // An odd number of out-of-place launches on level l left copy 1 current: copy
 // it back so that every level ends each V-cycle on copy 0.
 template <typename T>
@@ -1239,6 +1305,10 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int so
             }
             tiled(c, H, false, d, rem, 1, false, act, pre_cls, rhs && first, first ? psh : nullptr,
                   zero && first);
+        } else if (kPlain && c->lay.brick[d] > 0) {
+            if constexpr (kPlain)
+                bricks(c, H, d, nu1, 1, act, pre_cls, false, d > 0,
+                       d == 0 && c->shift_in_cycle ? c->res : nullptr);
         } else {
             if (z3_at(c, d)) {
                 // on the finest level the first step takes the zero correction
@@ -1268,7 +1338,8 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int so
         // level d + 1's right-hand side f = fr + N(u), unless its first tiled
         // launch forms it (tail levels: the tail does)
         const bool fused_next =
-            tiled2d(c) && nu_pre(o, d + 1) > 0 && d + 1 < depth && !c->lay.strip[d + 1];
+            d + 1 < depth && (tiled2d(c) ? nu_pre(o, d + 1) > 0 && !c->lay.strip[d + 1]
+                                         : c->lay.brick[d + 1] > 0);
         if (!fused_next && c->Bcs[d].n > 0) {
             TimedScope t(c, xfer_cls);
             chhs::launch_coarse_rhs(dim, make_batch(H.dev, H.cur, d, act), c->Bcs[d].dev,
@@ -1317,6 +1388,14 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int so
                       true);
                 first = false;
             }
+        } else if (kPlain && c->lay.brick[d] > 0) {
+            if (bil) {
+                TimedScope t(c, xfer_cls);
+                chhs::launch_prolong(dim, make_batch(H.dev, H.cur, d, act), c->B[d].dev, c->B[d].n,
+                                     true, c->stream);
+            }
+            if constexpr (kPlain)
+                bricks(c, H, d, nu2, d == 0 ? 2 : 0, act, post_cls, !bil, false, nullptr);
         } else {
             // the fused 3D step takes the prolongation into its first launch
             const bool pro3 = z3_at(c, d) && nu2 > 0;
@@ -1466,7 +1545,7 @@ int autotune3(chhs_ctx* c) {
     c->opts.timing = 0;
     int rc = CHHS_OK;
     for (int l = 0; l < c->lay.depth && rc == CHHS_OK; ++l) {
-        if ((c->mixed ? c->Z32[l].n : c->Z64[l].n) == 0) continue;
+        if ((c->mixed ? c->Z32[l].n : c->Z64[l].n) == 0 || c->lay.brick[l] > 0) continue;
         float t[2];
         for (int k = 0; k < 2 && rc == CHHS_OK; ++k) {
             c->lay.z3[l] = k == 1;
@@ -1645,7 +1724,7 @@ void fold_cells(chhs_ctx* c, bool n_only, const int* act, const double** src, co
 }
 
 // Plain FP64, every instance's finest level held by the tail with owner threads:
-// one launch runs the counted cycles of a step (16^2: 333 -> 150 us a step).
+// one launch runs the counted cycles of a step (16^2: 333 -> 203 us a step).
 bool whole_in_tail(const chhs_ctx* c) {
     return !c->mixed && c->lay.tail_parts == c->n_inst && c->opts.timing == 0;
 }
@@ -1660,8 +1739,9 @@ void enqueue_plain_cycle(chhs_ctx* c, bool count, int buf) {
     const chhs_opts& o = c->opts;
     enqueue_vcycle(c, hier64(c));
     TimedScope t(c, CHHS_K_NORM);
-    // 3D: the z-marching residual over the finest level's fused-step tasks
-    if (c->dim == 3 && c->Z64[0].n > 0)
+    // 3D, not in bricks: the z-marching residual over the finest level's
+    // fused-step tasks
+    if (c->dim == 3 && c->lay.brick[0] == 0 && c->Z64[0].n > 0)
         chhs::launch_residual3d_partials(batch(c, 0, act), c->Z64[0].dev, c->Z64[0].n,
                                          level0_partials(c), c->stream);
     // instances without a fused finest-level norm: per-cell residual partials
@@ -2330,6 +2410,7 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
         rc |= upload(c->ZR64[l], b, L.off_ZR64[l], L.ZR64[l], st);
         rc |= upload(c->ZR32[l], b, L.off_ZR32[l], L.ZR32[l], st);
         rc |= upload(c->BcS[l], b, L.off_BcS[l], L.BcS[l], st);
+        rc |= upload(c->K[l], b, L.off_K[l], L.K[l], st);
     }
     rc |= upload(c->A0n, b, L.off_A0n, L.A0n, st);
     rc |= upload(c->A0t, b, L.off_A0t, L.A0t, st);
@@ -2377,9 +2458,9 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
         const int arc = autotune3(c);
         if (arc) return fail(arc);
     }
-    // 3D plain FP64 with the fused step on the finest level: its first
+    // 3D plain FP64 with the fused step or bricks on the finest level: the first
     // pre-smoothing launch subtracts p's pending mean as it loads p
-    if (!c->mixed && z3_at(c, 0) && o->nu1 > 0) c->shift_in_cycle = true;
+    if (!c->mixed && (z3_at(c, 0) || c->lay.brick[0] > 0) && o->nu1 > 0) c->shift_in_cycle = true;
     {
         // the per-step log of chhs_step_log, reserved up front
         const size_t per_step = size_t(n_inst) * chhs::kResStride * sizeof(double);

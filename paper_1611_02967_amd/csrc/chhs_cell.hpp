@@ -286,6 +286,40 @@ __device__ __forceinline__ void cell_operator(const Level<T>& L, int idx, int i,
     n2 = L.lam * sp + L.lam * L.gamma * samu;
 }
 
+// The same in 3D FP64 (the second-order scheme) as the bricks round it.
+__device__ __forceinline__ void cell_operator3(const Level<double>& L, int idx, int i, int j, int k,
+                                               double& n0, double& n1, double& n2) {
+    const double phic = L.phi[idx], muc = L.mu[idx], pc = L.p[idx], psc = L.pstar[idx];
+    CellDiffs q;
+    for_each_face<3>(i, j, k, L.nx, L.ny, L.nz, idx, [&](bool h, int nb) {
+        const double ps = L.pstar[nb], dmu = L.mu[nb] - muc, dp = L.p[nb] - pc,
+                     dphi = L.phi[nb] - phic;
+        CellDiffs t = q;
+        t.face(L.gamma, psc, ps, dmu, dp, dphi);
+        q.smm = h ? t.smm : q.smm;
+        q.sap = h ? t.sap : q.sap;
+        q.sphi = h ? t.sphi : q.sphi;
+        q.sp = h ? t.sp : q.sp;
+        q.samu = h ? t.samu : q.samu;
+    });
+    double n[3];
+    cell_apply(q, L.lam, L.kap, L.gamma, phic, muc, L.psi[idx], n);
+    n0 = n[0];
+    n1 = n[1];
+    n2 = n[2];
+}
+// N(u) for the transfers between levels.
+template <int DIM, typename T, bool CORR>
+__device__ __forceinline__ void transfer_operator(const Level<T>& L, int idx, int i, int j, int k,
+                                                  T& n0, T& n1, T& n2) {
+    if constexpr (DIM == 3 && sizeof(T) == 8 && !CORR)
+        if (L.order != 1) {
+            cell_operator3(L, idx, i, j, k, n0, n1, n2);
+            return;
+        }
+    cell_operator<DIM, T, CORR>(L, idx, i, j, k, n0, n1, n2);
+}
+
 // Collective (phi, mu, p) update of one cell with its neighbours frozen and chi
 // linearised at the current phi (one local Newton step).  The three local rows
 //   phi + lam SM mu + lam Sa p        = b1
@@ -344,6 +378,38 @@ __device__ __forceinline__ void cell_solve(const Level<T>& L, int idx, int i, in
     mu_o = (b2 + bb * b1r) * inv_det;
     phi_o = (b1r - ared * b2) * inv_det;
     p_o = -(b3 * inv_lam + gam * sa * mu_o) * inv_nf;
+}
+
+// cell_solve of the per-color launches: in 3D FP64 (the second-order scheme) as
+// the bricks round it.
+template <int DIM, typename T, bool CORR = false, bool L0 = false>
+__device__ __forceinline__ void smooth_cell(const Level<T>& L, int idx, int i, int j, int k,
+                                            T inv_lam, T& phi_o, T& mu_o, T& p_o) {
+    if constexpr (DIM == 3 && sizeof(T) == 8 && !CORR) {
+        if (L.order != 1) {
+            const T psc = L.pstar[idx];
+            int nf = 0;
+            CellSums q;
+            for_each_face<DIM>(i, j, k, L.nx, L.ny, L.nz, idx, [&](bool h, int nb) {
+                const T ps = L.pstar[nb], mun = L.mu[nb], pn = L.p[nb], phin = L.phi[nb];
+                CellSums t = q;
+                t.face(L.gamma, psc, ps, mun, pn, phin);
+                nf += h ? 1 : 0;
+                q.sa = h ? t.sa : q.sa;
+                q.sa2 = h ? t.sa2 : q.sa2;
+                q.smmu = h ? t.smmu : q.smmu;
+                q.sphi = h ? t.sphi : q.sphi;
+                q.sp = h ? t.sp : q.sp;
+                q.sap = h ? t.sap : q.sap;
+                q.samu = h ? t.samu : q.samu;
+            });
+            const T psi = L.psi[idx];
+            cell_update(q, nf, L.lam, inv_lam, L.kap, L.gamma, L.phi[idx], psi, L0 ? psi : L.f0[idx],
+                        L.f1[idx], L0 ? T(0) : L.f2[idx], phi_o, mu_o, p_o);
+            return;
+        }
+    }
+    cell_solve<DIM, T, CORR, L0>(L, idx, i, j, k, inv_lam, phi_o, mu_o, p_o);
 }
 
 }  // namespace chhs

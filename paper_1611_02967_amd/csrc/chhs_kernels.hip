@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kBlock) void k_smooth(Batch<T> b, const CellTask* _
     decode<DIM>(idx, L.nx, L.ny, i, j, k);
     if (((i + j + k) & 1) != color) return;
     T phi, mu, p;
-    cell_solve<DIM, T, CORR, L0>(L, idx, i, j, k, T(1) / L.lam, phi, mu, p);
+    smooth_cell<DIM, T, CORR, L0>(L, idx, i, j, k, T(1) / L.lam, phi, mu, p);
     L.phi[idx] = phi;
     L.mu[idx] = mu;
     L.p[idx] = p;
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kBlock) void k_smooth_color(Batch<T> b, const CellT
     const int i = 2 * m + ((j + k + color) & 1);
     const int idx = row * L.nx + i;
     T phi, mu, p;
-    cell_solve<DIM, T, CORR, L0>(L, idx, i, j, k, T(1) / L.lam, phi, mu, p);
+    smooth_cell<DIM, T, CORR, L0>(L, idx, i, j, k, T(1) / L.lam, phi, mu, p);
     L.phi[idx] = phi;
     L.mu[idx] = mu;
     L.p[idx] = p;
@@ -346,7 +346,7 @@ __device__ __forceinline__ void child_values(const Level<T>& F, int fi, int fj, 
                                              T (&v)[7]) {
     const int f = (fk * F.ny + fj) * F.nx + fi;
     T n0, n1, n2;
-    cell_operator<DIM, T, CORR>(F, f, fi, fj, fk, n0, n1, n2);
+    transfer_operator<DIM, T, CORR>(F, f, fi, fj, fk, n0, n1, n2);
     v[0] = F.f0[f] - n0;
     v[1] = F.f1[f] - n1;
     v[2] = F.f2[f] - n2;
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kBlock) void k_coarse_rhs(Batch<T> b,
     int i, j, k;
     decode<DIM>(idx, C.nx, C.ny, i, j, k);
     T n0, n1, n2;
-    cell_operator<DIM, T, CORR>(C, idx, i, j, k, n0, n1, n2);
+    transfer_operator<DIM, T, CORR>(C, idx, i, j, k, n0, n1, n2);
     C.f0[idx] = C.fr0[idx] + n0;
     C.f1[idx] = C.fr1[idx] + n1;
     C.f2[idx] = C.fr2[idx] + n2;
