@@ -90,7 +90,7 @@ struct Layout {
     int zseg64[kMaxLevels] = {}, zseg32[kMaxLevels] = {};
     // 3D level smoothed by the fused step (else by one launch per color)
     bool z3[kMaxLevels] = {};
-    // 3D FP64 level smoothed in bricks: steps per launch (0: not); its bricks
+    // 3D level smoothed in bricks: steps per launch (0: not); its bricks
     int brick[kMaxLevels] = {};
     std::vector<std::vector<BrickTask>> K;
     bool strip[kMaxLevels] = {};            // level smoothed by the row-streaming kernel
@@ -551,7 +551,7 @@ void level0_ranges(Layout& L, int n_inst) {
                 at += n;
             }
     }
-    else if (L.brick[0] > 0)
+    else if (L.brick[0] > 0 && L.desc32.empty())
         task_ranges(L.rngT0, n_inst, L.K[0]);
     else
         task_ranges(L.rngT0, n_inst, L.Z64[0]);     // 3D
@@ -614,7 +614,7 @@ int step3_seg(const std::vector<int>& nxs, const std::vector<int>& nys, const st
     return 8;
 }
 
-// Bricks of one FP64 3D level over the listed instances (extents, -1 = skip) and
+// Bricks of one 3D level over the listed instances (extents, -1 = skip) and
 // the steps per launch, 0 for no bricks.  A finest level is in bricks if no
 // instance has more than kBrickFinest cells there (by instance, as the sums of
 // the norm and of p's mean follow the bricks and a batched instance keeps the
@@ -625,7 +625,8 @@ int step3_seg(const std::vector<int>& nxs, const std::vector<int>& nys, const st
 // once.  Two steps of the scheme, per-color launches / bricks: 16^3 928 / 583
 // us, 32^3 1509 / 903, 48 x 32 x 64 2020 / 1253, 64^3 (coarse levels) 2442 /
 // 1886, 64 grids of 16^3 1306 / 1195; beyond: 80^3 with its finest level per
-// color 2675 us, in bricks 2843, 8 grids of 64^3 6187 and 6588.
+// color 2675 us, in bricks 2843, 8 grids of 64^3 6187 and 6588.  Mixed precision:
+// 32^3 1533 / 1047, 48 x 32 x 64 2062 / 1393, 64^3 2426 / 1880, 128^3 6783 / 6117.
 constexpr long kBrickFinest = 1L << 17, kBrickCoarse = 1L << 18;
 constexpr long kBrickTwo = 256;
 int brick_tasks(std::vector<BrickTask>& out, bool finest, const std::vector<int>& nxs,
@@ -928,7 +929,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
             // (the autotuner may choose anew)
             const int zs = mixed ? L.zseg32[l] : L.zseg64[l];
             L.z3[l] = o->smoother == 4 || zs >= kStep3MinSeg;
-            if (o->smoother == 0 && !mixed && !L.z3[l] && nu_pre(*o, l) > 0 && nu_post(*o, l) > 0)
+            if (o->smoother == 0 && !L.z3[l] && nu_pre(*o, l) > 0 && nu_post(*o, l) > 0)
                 L.brick[l] = brick_tasks(L.K[l], l == 0, lnx_t[l], lny[l], lnz[l]);
         }
     // 3D restriction per instance (never by what else the batch holds): the
@@ -1207,16 +1208,18 @@ void step3(chhs_ctx* c, const Hier<T>& H, int l, const int* active, int cls, int
 // Smoothing launches on a level in bricks: n steps on level l, `last` in the
 // last launch (epi of launch_brick3d), the prolongation, the right-hand side or
 // the pending mean of p in the first; flips the level's current copy.
-void bricks(chhs_ctx* c, const Hier<double>& H, int l, int n, int last, const int* active, int cls,
+template <typename T>
+void bricks(chhs_ctx* c, const Hier<T>& H, int l, int n, int last, const int* active, int cls,
             bool pro, bool rhs, const double* psh) {
     for (bool first = true; n > 0; first = false) {
         const int k = std::min(n, c->lay.brick[l]);
         n -= k;
-        Batch<double> b = make_batch(H.dev, H.cur, l, active);
+        Batch<T> b = make_batch(H.dev, H.cur, l, active);
         b.pshift = first ? psh : nullptr;
         {
             TimedScope t(c, cls);
-            chhs::launch_brick3d(b, c->K[l].dev, c->K[l].n, l == 0, k, n == 0 ? last : 0,
+            chhs::launch_brick3d(b, c->K[l].dev, c->K[l].n,
+                                 std::is_same<T, double>::value && l == 0, k, n == 0 ? last : 0,
                                  pro && first, rhs && first, level0_partials(c), c->stream);
         }
         H.cur[l] ^= 1;
@@ -1305,10 +1308,9 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int so
             }
             tiled(c, H, false, d, rem, 1, false, act, pre_cls, rhs && first, first ? psh : nullptr,
                   zero && first);
-        } else if (kPlain && c->lay.brick[d] > 0) {
-            if constexpr (kPlain)
-                bricks(c, H, d, nu1, 1, act, pre_cls, false, d > 0,
-                       d == 0 && c->shift_in_cycle ? c->res : nullptr);
+        } else if (c->lay.brick[d] > 0) {
+            bricks(c, H, d, nu1, 1, act, pre_cls, false, d > 0,
+                   kPlain && d == 0 && c->shift_in_cycle ? c->res : nullptr);
         } else {
             if (z3_at(c, d)) {
                 // on the finest level the first step takes the zero correction
@@ -1388,14 +1390,13 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int so
                       true);
                 first = false;
             }
-        } else if (kPlain && c->lay.brick[d] > 0) {
+        } else if (c->lay.brick[d] > 0) {
             if (bil) {
                 TimedScope t(c, xfer_cls);
                 chhs::launch_prolong(dim, make_batch(H.dev, H.cur, d, act), c->B[d].dev, c->B[d].n,
                                      true, c->stream);
             }
-            if constexpr (kPlain)
-                bricks(c, H, d, nu2, d == 0 ? 2 : 0, act, post_cls, !bil, false, nullptr);
+            bricks(c, H, d, nu2, kPlain && d == 0 ? 2 : 0, act, post_cls, !bil, false, nullptr);
         } else {
             // the fused 3D step takes the prolongation into its first launch
             const bool pro3 = z3_at(c, d) && nu2 > 0;

@@ -1,4 +1,5 @@
-// Smoothing of small FP64 3D levels in bricks, batched over instances.
+// Smoothing of small 3D levels in bricks, batched over instances: FP64, or (T =
+// float) the correction form.
 //
 // One workgroup owns a brick of 8 x 4 x 4 cells of one instance (a BrickTask)
 // and stages it in LDS with the cells around it that its result depends on.  It
@@ -37,11 +38,14 @@
 // touch consecutive words.
 #include "chhs_cell.hpp"
 
+#include <type_traits>
+
 namespace chhs {
 namespace {
 
 constexpr int TX = kBrickX, TY = kBrickY, TZ = kBrickZ;
-typedef double D2 __attribute__((ext_vector_type(2)));
+template <typename T>
+using V2 = T __attribute__((ext_vector_type(2)));
 
 constexpr int dist1(int v, int n) { return v < 0 ? -v : (v >= n ? v - n + 1 : 0); }
 
@@ -85,14 +89,16 @@ struct Slots {
 template <int H>
 __constant__ constexpr Slots<H> kSlots{};
 
-template <bool L0, int NS, int EPI, bool PRO, bool RHS>
+template <typename T, bool L0, int NS, int EPI, bool PRO, bool RHS>
 __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void k_brick3d(
-    Batch<double> bt, const BrickTask* __restrict__ tasks, int ntasks, double* partial) {
+    Batch<T> bt, const BrickTask* __restrict__ tasks, int ntasks, double* partial) {
+    constexpr bool CORR = std::is_same<T, float>::value;
+    using D2 = V2<T>;
     constexpr int X = EPI ? 1 : 0, H = X + 2 * NS;
     using G = Slots<H>;
     constexpr int PW = G::PW, SY = 2 * PW, SZ = 2 * PW * G::R;
     static_assert(PW <= 16 && G::R <= 16 && G::D <= 16, "slot fields");
-    __shared__ double s_phi[G::W], s_mu[G::W], s_p[G::W], s_ps[G::W];
+    __shared__ T s_phi[G::W], s_mu[G::W], s_p[G::W], s_ps[G::W];
 
     // XCD x takes a contiguous range of tasks (a bijection on [0, ntasks)):
     // neighbouring bricks share their halo through one L2
@@ -102,11 +108,11 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
     const int task = xcd * q8 + (xcd < rem ? xcd : rem) + jj;
     const BrickTask tk = tasks[task];
     if (bt.active != nullptr && bt.active[tk.inst] == 0) return;
-    const Level<double> L = make_view(bt.desc[tk.inst * kMaxLevels + bt.level], bt.cur);
-    const Level<double> C = make_view(bt.desc[tk.inst * kMaxLevels + bt.level + 1], bt.cur_c);
+    const Level<T> L = make_view(bt.desc[tk.inst * kMaxLevels + bt.level], bt.cur);
+    const Level<T> C = make_view(bt.desc[tk.inst * kMaxLevels + bt.level + 1], bt.cur_c);
     const int nx = L.nx, ny = L.ny, nz = L.nz;
     const int tid = threadIdx.x;
-    const double psh = bt.pshift != nullptr ? bt.pshift[tk.inst * kResStride + 4] : 0.0;
+    const double psh = !CORR && bt.pshift != nullptr ? bt.pshift[tk.inst * kResStride + 4] : 0.0;
 
     const unsigned sl = kSlots<H>.v[tid < G::N ? tid : 0];
     const int rp = int(sl & 15), ry = int(sl >> 4 & 15), rz = int(sl >> 8 & 15);
@@ -120,9 +126,9 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
     const int da = in ? int(sl >> 12 & 15) : kFar, db = in ? int(sl >> 16 & 15) : kFar;
 
     D2 phi = {0, 0}, mu = {0, 0}, p = {0, 0}, ps = {0, 0}, psi = {0, 0}, f0 = {0, 0}, f1 = {0, 0},
-       f2 = {0, 0};
+       f2 = {0, 0}, bs = {0, 0};
     if (in) {
-        auto ld = [&](const double* a) { return gload(reinterpret_cast<const D2*>(a), g >> 1); };
+        auto ld = [&](const T* a) { return gload(reinterpret_cast<const D2*>(a), g >> 1); };
         phi = ld(L.phi);
         mu = ld(L.mu);
         p = ld(L.p);
@@ -133,6 +139,7 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
             f0 = ld(RHS ? L.fr0 : L.f0);
             f2 = ld(RHS ? L.fr2 : L.f2);
         }
+        if (CORR) bs = ld(L.b);
         if (PRO) {
             const int c = ((gz >> 1) * C.ny + (gy >> 1)) * C.nx + (gx >> 1);
             phi += gload(C.phi, c) - gload(C.ub0, c);
@@ -140,7 +147,7 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
             p += gload(C.p, c) - gload(C.ub2, c);
         }
         if (L0) f0 = psi;
-        p -= psh;
+        if (!CORR) p -= T(psh);
         s_phi[w0] = phi.x, s_phi[w1] = phi.y;
         s_mu[w0] = mu.x, s_mu[w1] = mu.y;
         s_p[w0] = p.x, s_p[w1] = p.y;
@@ -148,8 +155,8 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
     }
     __syncthreads();
 
-    const double lam = L.lam, kap = L.kap, gam = L.gamma;
-    const double inv_lam = 1.0 / lam;
+    const T lam = L.lam, kap = L.kap, gam = L.gamma;
+    const T inv_lam = T(1) / lam;
     const bool hy0 = gy > 0, hy1 = gy < ny - 1, hz0 = gz > 0, hz1 = gz < nz - 1;
     // fn(word) for the interior faces of member e in the order x - 1, x + 1,
     // y - 1, y + 1, z - 1, z + 1
@@ -162,24 +169,28 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
         if (hz0) fn(w - SZ);
         if (hz1) fn(w + SZ);
     };
-    auto apply = [&](int e, double ps_e, double psi_e, double (&n)[3]) {
+    auto apply = [&](int e, T (&n)[3]) {
         const int w = e ? w1 : w0;
-        const double phic = s_phi[w], muc = s_mu[w], pc = s_p[w];
-        CellDiffs d;
+        const T phic = s_phi[w], muc = s_mu[w], pc = s_p[w];
+        const T ps_e = e ? ps.y : ps.x, psi_e = e ? psi.y : psi.x;
+        Diffs<T> d;
         faces(e, [&](int wn) {
             d.face(gam, ps_e, s_ps[wn], s_mu[wn] - muc, s_p[wn] - pc, s_phi[wn] - phic);
         });
-        cell_apply(d, lam, kap, gam, phic, muc, psi_e, n);
+        if constexpr (CORR)
+            cell_apply(d, lam, kap, gam, phic, muc, psi_e, e ? bs.y : bs.x, n);
+        else
+            cell_apply(d, lam, kap, gam, phic, muc, psi_e, n);
     };
 
     if (RHS) {
-        double n[3];
+        T n[3];
         if (da <= H - 1) {
-            apply(0, ps.x, psi.x, n);
+            apply(0, n);
             f0.x += n[0], f1.x += n[1], f2.x += n[2];
         }
         if (db <= H - 1) {
-            apply(1, ps.y, psi.y, n);
+            apply(1, n);
             f0.y += n[0], f1.y += n[1], f2.y += n[2];
         }
         if (tid < 64 && in) {
@@ -197,13 +208,18 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
         const int e = e0 ^ (ph & 1);
         if ((e ? db : da) <= X + 2 * NS - 1 - ph) {
             const int w = e ? w1 : w0;
-            const double ps_e = e ? ps.y : ps.x;
-            CellSums q;
+            const T ps_e = e ? ps.y : ps.x, psi_e = e ? psi.y : psi.x;
+            const T f0_e = e ? f0.y : f0.x, f1_e = e ? f1.y : f1.x, f2_e = e ? f2.y : f2.x;
+            Sums<T> q;
             faces(e, [&](int wn) { q.face(gam, ps_e, s_ps[wn], s_mu[wn], s_p[wn], s_phi[wn]); });
             const int nf = nfyz + (gx + e > 0 ? 1 : 0) + (gx + e < nx - 1 ? 1 : 0);
-            double phin, mun, pn;
-            cell_update(q, nf, lam, inv_lam, kap, gam, s_phi[w], e ? psi.y : psi.x, e ? f0.y : f0.x,
-                        e ? f1.y : f1.x, e ? f2.y : f2.x, phin, mun, pn);
+            T phin, mun, pn;
+            if constexpr (CORR)
+                cell_update(q, nf, lam, inv_lam, kap, gam, s_phi[w], psi_e, e ? bs.y : bs.x, f0_e,
+                            f1_e, f2_e, phin, mun, pn);
+            else
+                cell_update(q, nf, lam, inv_lam, kap, gam, s_phi[w], psi_e, f0_e, f1_e, f2_e, phin,
+                            mun, pn);
             s_phi[w] = phin;
             s_mu[w] = mun;
             s_p[w] = pn;
@@ -220,22 +236,22 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
         gstore(reinterpret_cast<D2*>(L.p_alt), g >> 1, up);
     }
     if (EPI == 0) return;
-    double ra[3] = {0, 0, 0}, rb[3] = {0, 0, 0};
+    T ra[3] = {0, 0, 0}, rb[3] = {0, 0, 0};
     if (in) {
-        apply(0, ps.x, psi.x, ra);
-        apply(1, ps.y, psi.y, rb);
+        apply(0, ra);
+        apply(1, rb);
         ra[0] = f0.x - ra[0], ra[1] = f1.x - ra[1], ra[2] = f2.x - ra[2];
         rb[0] = f0.y - rb[0], rb[1] = f1.y - rb[1], rb[2] = f2.y - rb[2];
     }
     if (EPI == 1) {
         // children of a coarse cell: the pair, lanes ^ 4 (y) and ^ 16 (z)
-        double v[6] = {ra[0] + rb[0],   ra[1] + rb[1], ra[2] + rb[2],
-                       uphi.x + uphi.y, umu.x + umu.y, up.x + up.y};
+        T v[7] = {ra[0] + rb[0], ra[1] + rb[1], ra[2] + rb[2], uphi.x + uphi.y,
+                  umu.x + umu.y, up.x + up.y,   bs.x + bs.y};
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
+        for (int k = 0; k < (CORR ? 7 : 6); ++k) {
             v[k] += __shfl_xor(v[k], 4, 64);
             v[k] += __shfl_xor(v[k], 16, 64);
-            v[k] *= 0.125;
+            v[k] *= T(0.125);
         }
         if (!in) return;
         const int c = ((gz >> 1) * C.ny + (gy >> 1)) * C.nx + (gx >> 1);
@@ -248,7 +264,9 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
         if (sub == 1) gstore(C.phi, c, v[3]), gstore(C.ub0, c, v[3]);
         if (sub == 2) gstore(C.mu, c, v[4]), gstore(C.ub1, c, v[4]);
         if (sub == 3) gstore(C.p, c, v[5]), gstore(C.ub2, c, v[5]);
-    } else {
+        if (CORR && sub == 1) gstore(C.b, c, v[6]);
+    }
+    if constexpr (EPI == 2) {
         double v[4] = {__builtin_fma(rb[0], rb[0], ra[0] * ra[0]),
                        __builtin_fma(rb[1], rb[1], ra[1] * ra[1]),
                        __builtin_fma(rb[2], rb[2], ra[2] * ra[2]), in ? up.x + up.y : 0.0};
@@ -259,54 +277,61 @@ __global__ __launch_bounds__((Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63) void
     }
 }
 
-template <bool L0, int NS, int EPI, bool PRO, bool RHS>
-void launch(const Batch<double>& b, const BrickTask* t, int nt, double* partial, hipStream_t st) {
+template <typename T, bool L0, int NS, int EPI, bool PRO, bool RHS>
+void launch(const Batch<T>& b, const BrickTask* t, int nt, double* partial, hipStream_t st) {
     constexpr int threads = (Slots<(EPI ? 1 : 0) + 2 * NS>::N + 63) & ~63;
-    hipLaunchKernelGGL((k_brick3d<L0, NS, EPI, PRO, RHS>), dim3(nt), dim3(threads), 0, st, b, t, nt,
-                       partial);
+    hipLaunchKernelGGL((k_brick3d<T, L0, NS, EPI, PRO, RHS>), dim3(nt), dim3(threads), 0, st, b, t,
+                       nt, partial);
 }
 
-template <bool L0, int NS>
-void launch_ns(const Batch<double>& b, const BrickTask* t, int nt, int epi, bool pro, bool rhs,
+template <typename T, bool L0, int NS>
+void launch_ns(const Batch<T>& b, const BrickTask* t, int nt, int epi, bool pro, bool rhs,
                double* partial, hipStream_t st) {
     if constexpr (L0) {
         if (epi == 2) {
             if (pro)
-                launch<L0, NS, 2, true, false>(b, t, nt, partial, st);
+                launch<T, L0, NS, 2, true, false>(b, t, nt, partial, st);
             else
-                launch<L0, NS, 2, false, false>(b, t, nt, partial, st);
+                launch<T, L0, NS, 2, false, false>(b, t, nt, partial, st);
             return;
         }
     } else if (rhs) {
         if (epi == 1)
-            launch<L0, NS, 1, false, true>(b, t, nt, partial, st);
+            launch<T, L0, NS, 1, false, true>(b, t, nt, partial, st);
         else
-            launch<L0, NS, 0, false, true>(b, t, nt, partial, st);
+            launch<T, L0, NS, 0, false, true>(b, t, nt, partial, st);
         return;
     }
     if (epi == 1)
-        launch<L0, NS, 1, false, false>(b, t, nt, partial, st);
+        launch<T, L0, NS, 1, false, false>(b, t, nt, partial, st);
     else if (pro)
-        launch<L0, NS, 0, true, false>(b, t, nt, partial, st);
+        launch<T, L0, NS, 0, true, false>(b, t, nt, partial, st);
     else
-        launch<L0, NS, 0, false, false>(b, t, nt, partial, st);
+        launch<T, L0, NS, 0, false, false>(b, t, nt, partial, st);
 }
 
 }  // namespace
 
-void launch_brick3d(const Batch<double>& b, const BrickTask* t, int nt, bool level0, int ns, int epi,
+template <typename T>
+void launch_brick3d(const Batch<T>& b, const BrickTask* t, int nt, bool level0, int ns, int epi,
                     bool pro, bool rhs, double* partial, hipStream_t st) {
     if (nt == 0) return;
-    if (level0) {
-        if (ns == 2)
-            launch_ns<true, 2>(b, t, nt, epi, pro, rhs, partial, st);
-        else
-            launch_ns<true, 1>(b, t, nt, epi, pro, rhs, partial, st);
-    } else if (ns == 2) {
-        launch_ns<false, 2>(b, t, nt, epi, pro, rhs, partial, st);
-    } else {
-        launch_ns<false, 1>(b, t, nt, epi, pro, rhs, partial, st);
-    }
+    if constexpr (std::is_same<T, double>::value)
+        if (level0) {
+            if (ns == 2)
+                launch_ns<T, true, 2>(b, t, nt, epi, pro, rhs, partial, st);
+            else
+                launch_ns<T, true, 1>(b, t, nt, epi, pro, rhs, partial, st);
+            return;
+        }
+    if (ns == 2)
+        launch_ns<T, false, 2>(b, t, nt, epi, pro, rhs, partial, st);
+    else
+        launch_ns<T, false, 1>(b, t, nt, epi, pro, rhs, partial, st);
 }
+template void launch_brick3d(const Batch<double>&, const BrickTask*, int, bool, int, int, bool, bool,
+                             double*, hipStream_t);
+template void launch_brick3d(const Batch<float>&, const BrickTask*, int, bool, int, int, bool, bool,
+                             double*, hipStream_t);
 
 }  // namespace chhs

@@ -159,28 +159,42 @@ __device__ __forceinline__ float recip_ge1(float x) {
     return __builtin_fmaf(r, e, r);
 }
 
-// The same update and operator in FP64 with every rounding written out (no
+// a b + c, rounded once.
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// The sum of the correction form's chi (nonlin): chi = x / 4 times it.
+template <typename T>
+__device__ __forceinline__ T chi_sum(T x, T psi, T b) {
+#pragma clang fp contract(off)
+    const T c = fma_of(psi, psi, fma_of(b, T(3) * b, psi * (b + b)));
+    return fma_of(x, x, fma_of(x, fma_of(T(3), b, psi), c));
+}
+
+// The same update and operator with every rounding written out (no
 // contraction left to the compiler), for kernels of several shapes that must
-// give the same bits: cell_sums is fed the faces in the order x - 1, x + 1,
-// y - 1, y + 1 (, z - 1, z + 1).  The nonlinear term is kept as a polynomial of
+// give the same bits: CellSums is fed the faces in the order x - 1, x + 1,
+// y - 1, y + 1 (, z - 1, z + 1).  In FP64 the nonlinear term is kept as a polynomial of
 // phi: chi' = d0 + phi (c1 + 3/4 phi), chi - chi' phi = psi^3 / 4 - phi^2 (c1 + phi) / 2
 // with d0 = psi^2 / 4, c1 = psi / 2 (a third fewer operations than chi and chi'
-// apart).
-struct CellSums {
-    double sa = 0, sa2 = 0, smmu = 0, sphi = 0, sp = 0, sap = 0, samu = 0;
-    __device__ __forceinline__ void face(double gam, double psc, double psn, double mun, double pn,
-                                         double phin) {
+// apart).  The FP32 correction form is rounded as the compiler contracts
+// cell_solve and cell_operator in the per-cell kernels, whose bits it keeps.
+template <typename T>
+struct Sums {
+    T sa = 0, sa2 = 0, smmu = 0, sphi = 0, sp = 0, sap = 0, samu = 0;
+    __device__ __forceinline__ void face(T gam, T psc, T psn, T mun, T pn, T phin) {
 #pragma clang fp contract(off)
-        const double a = 0.5 * (psc + psn);
+        const T a = T(0.5) * (psc + psn);
         sa = sa + a;
-        sa2 = __builtin_fma(a, a, sa2);
-        smmu = __builtin_fma(__builtin_fma(a, gam * a, 1.0), mun, smmu);
+        sa2 = fma_of(a, a, sa2);
+        smmu = fma_of(fma_of(a, gam * a, T(1)), mun, smmu);
         sphi = sphi + phin;
         sp = sp + pn;
-        sap = __builtin_fma(a, pn, sap);
-        samu = __builtin_fma(a, mun, samu);
+        sap = fma_of(a, pn, sap);
+        samu = fma_of(a, mun, samu);
     }
 };
+typedef Sums<double> CellSums;
 __device__ __forceinline__ void cell_update(const CellSums& q, int nf, double lam, double inv_lam,
                                             double kap, double gam, double x, double psi, double f0,
                                             double f1, double f2, double& phi, double& mu,
@@ -204,20 +218,44 @@ __device__ __forceinline__ void cell_update(const CellSums& q, int nf, double la
     phi = __builtin_fma(-ared, b2, b1r) * inv_det;
     p = -(inv_nf * __builtin_fma(inv_lam, b3, (gam * q.sa) * mu));
 }
-// N(u) of one cell from the differences to its neighbours.
-struct CellDiffs {
-    double smm = 0, sap = 0, sphi = 0, sp = 0, samu = 0;
-    __device__ __forceinline__ void face(double gam, double psc, double psn, double dmu, double dp,
-                                         double dphi) {
+// The correction form (base state b).
+__device__ __forceinline__ void cell_update(const Sums<float>& q, int nf, float lam, float inv_lam,
+                                            float kap, float gam, float x, float psi, float b,
+                                            float f0, float f1, float f2, float& phi, float& mu,
+                                            float& p) {
 #pragma clang fp contract(off)
-        const double a = 0.5 * (psc + psn);
-        smm = __builtin_fma(__builtin_fma(a, gam * a, 1.0), dmu, smm);
-        sap = __builtin_fma(a, dp, sap);
+    const float fnf = float(nf);
+    const float inv_nf = nf == 6 ? 1.0f / 6.0f
+                       : (nf == 5 ? 1.0f / 5.0f
+                       : (nf == 4 ? 0.25f : (nf == 3 ? 1.0f / 3.0f : (nf == 2 ? 0.5f : 1.0f))));
+    const float y = b + x;
+    const float dchi = 0.25f * fma_of(psi, psi, fma_of(y, 3.0f * y, psi * (y + y)));
+    const float b1 = fma_of(lam, q.sap, fma_of(lam, q.smmu, f0));
+    const float b2 = fma_of(-kap, q.sphi, fma_of(-x, dchi, fma_of(0.25f * x, chi_sum(x, psi, b), f1)));
+    const float b3 = fma_of(-(lam * gam), q.samu, fma_of(-lam, q.sp, f2));
+    const float ared = lam * fma_of(gam, fma_of(-(q.sa * q.sa), inv_nf, q.sa2), fnf);
+    const float b1r = fma_of(q.sa * inv_nf, b3, b1);
+    const float bb = fma_of(kap, fnf, dchi);
+    const float inv_det = recip_ge1(fma_of(ared, bb, 1.0f));
+    mu = fma_of(bb, b1r, b2) * inv_det;
+    phi = fma_of(-ared, b2, b1r) * inv_det;
+    p = -(inv_nf * fma_of(inv_lam, b3, (gam * q.sa) * mu));
+}
+// N(u) of one cell from the differences to its neighbours.
+template <typename T>
+struct Diffs {
+    T smm = 0, sap = 0, sphi = 0, sp = 0, samu = 0;
+    __device__ __forceinline__ void face(T gam, T psc, T psn, T dmu, T dp, T dphi) {
+#pragma clang fp contract(off)
+        const T a = T(0.5) * (psc + psn);
+        smm = fma_of(fma_of(a, gam * a, T(1)), dmu, smm);
+        sap = fma_of(a, dp, sap);
         sphi = sphi + dphi;
         sp = sp + dp;
-        samu = __builtin_fma(a, dmu, samu);
+        samu = fma_of(a, dmu, samu);
     }
 };
+typedef Diffs<double> CellDiffs;
 __device__ __forceinline__ void cell_apply(const CellDiffs& q, double lam, double kap, double gam,
                                            double x, double mu, double psi, double (&n)[3]) {
 #pragma clang fp contract(off)
@@ -225,6 +263,13 @@ __device__ __forceinline__ void cell_apply(const CellDiffs& q, double lam, doubl
     n[1] = __builtin_fma(kap, q.sphi,
                          __builtin_fma(-0.25 * __builtin_fma(x, x, psi * psi), x + psi, mu));
     n[2] = __builtin_fma(lam, q.sp, (lam * gam) * q.samu);
+}
+__device__ __forceinline__ void cell_apply(const Diffs<float>& q, float lam, float kap, float gam,
+                                           float x, float mu, float psi, float b, float (&n)[3]) {
+#pragma clang fp contract(off)
+    n[0] = fma_of(-lam, q.sap, fma_of(-lam, q.smm, x));
+    n[1] = fma_of(kap, q.sphi, fma_of(-0.25f * x, chi_sum(x, psi, b), mu));
+    n[2] = fma_of(lam, q.sp, (lam * gam) * q.samu);
 }
 
 // Cell-centred bi/trilinear interpolation of the coarse correction cv - cb at

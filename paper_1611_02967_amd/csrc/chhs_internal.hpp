@@ -342,16 +342,18 @@ void launch_step3d(const Batch<double>& b, const Step3Task* t, int nt, int pro, 
 void launch_step3d(const Batch<float>& b, const Step3Task* t, int nt, int pro, int zero,
                    hipStream_t st);
 
-// ---- small FP64 3D levels in bricks (chhs_brick3d.hip) ------------------------------
+// ---- small 3D levels in bricks (chhs_brick3d.hip) -----------------------------------
 // ns (1 or 2) red-black steps on level b.level of every tasked instance, read
 // from copy b.cur and written to the other copy, in bricks of 8 x 4 x 4 cells
 // (even extents); epi 0 none, 1 residual + restriction into level + 1 (not with
 // pro), 2 norm partials of the finest level (kNormStride per task, in task
-// order); pro: piecewise-constant prolongation first; level0: f_phi = phi^m and f_p = 0 implied; rhs:
+// order); pro: piecewise-constant prolongation first; level0 (FP64): f_phi = phi^m and f_p = 0 implied; rhs:
 // the first launch on a coarse level, which forms f = fr + N(u) (not with
-// level0, pro or epi 2).  The second-order scheme only.
+// pro or epi 2; not on the finest level).  FP32: the correction form, which also
+// restricts b; no epi 2.  The second-order scheme only.
 constexpr int kBrickX = 8, kBrickY = 4, kBrickZ = 4;
-void launch_brick3d(const Batch<double>& b, const BrickTask* t, int nt, bool level0, int ns, int epi,
+template <typename T>
+void launch_brick3d(const Batch<T>& b, const BrickTask* t, int nt, bool level0, int ns, int epi,
                     bool pro, bool rhs, double* partial, hipStream_t st);
 
 // ---- single-workgroup coarse tail (chhs_tail.hip) ----------------------------------

@@ -73,18 +73,6 @@ struct Pair {
     }
 };
 
-// a b + c, rounded once.
-__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// The sum of the correction form's chi (nonlin): chi = x / 4 times it.
-template <typename T>
-__device__ __forceinline__ T chi_sum(T x, T psi, T b) {
-#pragma clang fp contract(off)
-    const T c = fma_of(psi, psi, fma_of(b, T(3) * b, psi * (b + b)));
-    return fma_of(x, x, fma_of(x, fma_of(T(3), b, psi), c));
-}
-
 // Scalars of a level.
 template <typename T>
 struct Coef {

@@ -1,4 +1,4 @@
-"""GPU tests of the 3D FP64 smoothing in bricks: the same bits as the per-color
+"""GPU tests of the 3D smoothing in bricks: the same bits as the per-color
 launches (opts.smoother = 3, which smooth, restrict, prolong and form right-hand
 sides cell by cell), and the oracle's V-cycle.
 """
@@ -67,6 +67,21 @@ def test_one_vcycle_in_bricks(chhs, shape, nu, prolong):
         assert np.max(np.abs(got[1][k] - want[1][k])) <= 1e-13 * scale, k
         assert np.max(np.abs(got[1][k] - u[k])) <= 1e-11 * scale, k
     assert abs(got[0] - want[0]) <= 1e-13 * want[0]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("nu,inner", [((2, 2), 1), ((1, 3), 2)])
+def test_one_correction_in_bricks_has_the_bits_of_the_per_color_launches(chhs, shape, nu, inner):
+    """Mixed precision, one refinement step: u + e with e from FP32 cycles."""
+    prm = scheme.Params(eps=0.05, gamma=2.0, s=1e-3, h=1.0 / shape[-1])
+    prev = uniform_field(shape, 9310, mean=0.1, amp=0.3)
+    cur = prev + uniform_field(shape, 9311, amp=0.05)
+    state = (prev, cur, uniform_field(shape, 9312, amp=0.3), uniform_field(shape, 9313, amp=0.01))
+    kw = dict(nu1=nu[0], nu2=nu[1], precision=1, inner_cycles=inner)
+    want = _vcycle(chhs, shape, prm, state, smoother=3, **kw)
+    got = _vcycle(chhs, shape, prm, state, **kw)
+    for k in range(2):
+        assert np.array_equal(got[1][k], want[1][k]), k
 
 
 def test_batch_with_bricks_of_one_and_two_steps_gives_the_single_runs_bits(chhs):
