@@ -1182,7 +1182,7 @@ void tiled(chhs_ctx* c, const Hier<T>& H, bool all, int l, int ns, int epi, bool
             const int* thr = post && c->lay.tile_threads_post[l] > 0 ? c->lay.tile_threads_post
                                                                      : c->lay.tile_threads;
             chhs::launch_tile2d<T>(b, tt.dev, tt.n, level0, ns, epi, pro,
-                                   tile_block(all ? 0 : thr[l], tt.n, std::is_same<T, double>::value), rhs,
+                                   all ? 512 : tile_block(thr[l], tt.n, std::is_same<T, double>::value), rhs,
                                    all ? c->lay.tile_y_all[l] : c->lay.tile_y[l], zero, part,
                                    c->stream);
         }

@@ -288,7 +288,8 @@ constexpr int kTileYTall = 32;
 // into level + 1 (copy b.cur_c), 2 residual-norm partials (4 per block, in task
 // order); pro: prolongation of level + 1's correction first; level0: f_phi =
 // phi^m and f_p = 0 implied; threads: 256, 512 or 1024 per block (four, two
-// or one pair of cells per thread);
+// or one pair of cells per thread; FP64 with 1024: k_block2d, a thread for each
+// pair within the halo's faces, even extents only);
 // rhs: first pre-smoothing launch on a coarse level, which first forms the FAS
 // right-hand side f += N(u) (not with level0, pro or epi 2); ty: tile height,
 // kTileY or (not with level0) kTileYSmall or kTileYTiny, as the tasks were cut,

@@ -40,7 +40,7 @@
 // touch consecutive LDS words.
 #pragma once
 
-#include "chhs_cell.hpp"
+#include "chhs_block2d.hpp"
 
 #include <type_traits>
 
@@ -49,10 +49,10 @@ namespace {
 
 constexpr int kTX = kTileX;     // block width (cells)
 
-// NT threads per block: 256, 512 or 1024 (four, two or one pair per thread),
-// chosen per level by the autotuner; without it 1024 on levels with fewer
-// tiles than compute units, where the time of one block is the time of the
-// launch, and 256 elsewhere.
+// NT threads per block: 256, 512 or (FP32) 1024, i.e. four, two or one pair per
+// thread; 1024 in FP64 is k_block2d, a thread per pair.  Chosen per level by the
+// autotuner; without it 1024 on levels with fewer tiles than compute units, where
+// the time of one block is the time of the launch, and 512 (FP32: 256) elsewhere.
 template <int NS, int EPI, int NT, int TY>
 struct Geometry {
     static constexpr int X = EPI ? 1 : 0;          // extra valid rings after the last phase
@@ -547,10 +547,19 @@ template <typename T, bool LEVEL0, int NS, int EPI, bool PRO, bool CORR, bool RH
           bool ZERO>
 void launch_ty(const Batch<T>& b, const TileTask* t, int nt, int threads, double* partial,
                hipStream_t st) {
-    if (threads == 1024)
+    if constexpr (!CORR) {
+        if (threads == 1024) {      // FP64, a thread per pair
+            constexpr int n = BlockSlots<(EPI ? 1 : 0) + 2 * NS, TY>::kThreads;
+            hipLaunchKernelGGL((k_block2d<LEVEL0, NS, EPI, PRO, RHS, TY>), dim3(nt), dim3(n), 0, st, b,
+                               t, nt, partial);
+            return;
+        }
+    } else if (threads == 1024) {
         hipLaunchKernelGGL((k_tile2d<T, LEVEL0, NS, EPI, PRO, CORR, 1024, RHS, TY, ZERO>), dim3(nt),
                            dim3(1024), 0, st, b, t, nt, partial);
-    else if (threads == 512)
+        return;
+    }
+    if (threads == 512)
         hipLaunchKernelGGL((k_tile2d<T, LEVEL0, NS, EPI, PRO, CORR, 512, RHS, TY, ZERO>), dim3(nt),
                            dim3(512), 0, st, b, t, nt, partial);
     else
