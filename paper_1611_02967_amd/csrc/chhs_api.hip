@@ -228,13 +228,10 @@ struct chhs_ctx {
     std::vector<Run> runs;
     int last_cycles = 0;            // cycles of the last step (the slowest instance's)
     bool graph_failed = false;
-    int capturing = -1;             // slot being captured, -1 when none
     // kernel timing (opts.timing)
     struct Pending { hipEvent_t a, b; int cls; };
     std::vector<hipEvent_t> ev_pool;
     std::vector<Pending> pending;        // resolved and recycled after each sync
-    std::vector<Pending> graph_pairs[2]; // recorded by every replay of a graph slot
-    int last_slot = -1;                  // slot replayed since the last synchronisation
     hipEvent_t cycle_done[2] = {nullptr, nullptr};   // end of a pipelined cycle per slot
     double t_ms[CHHS_K_COUNT] = {};
     int64_t t_n[CHHS_K_COUNT] = {};
@@ -1069,8 +1066,7 @@ bool timed(const chhs_ctx* c, int cls) {
 }
 
 // Brackets the launches issued during its lifetime with a pair of events on
-// the context stream when timing is enabled (captured into the graph when a
-// cycle is being captured).
+// the context stream when timing is enabled (timed contexts launch directly).
 class TimedScope {
   public:
     TimedScope(chhs_ctx* c, int cls) : c_(c), cls_(cls) {
@@ -1083,10 +1079,7 @@ class TimedScope {
         hipEvent_t b = pooled_event(c_);
         if (b == nullptr) return;
         (void)hipEventRecord(b, c_->stream);
-        if (c_->capturing >= 0)
-            c_->graph_pairs[c_->capturing].push_back({a_, b, cls_});
-        else
-            c_->pending.push_back({a_, b, cls_});
+        c_->pending.push_back({a_, b, cls_});
     }
 
   private:
@@ -1103,12 +1096,8 @@ void accumulate(chhs_ctx* c, const chhs_ctx::Pending& pe) {
     }
 }
 
-// After a stream synchronisation: accumulate the event pairs of the graph
-// replayed since the last one, and accumulate and recycle the eager pairs.
+// After a stream synchronisation: accumulate and recycle the event pairs.
 void resolve_timing(chhs_ctx* c) {
-    if (c->last_slot >= 0)
-        for (auto& pe : c->graph_pairs[c->last_slot]) accumulate(c, pe);
-    c->last_slot = -1;
     for (auto& pe : c->pending) {
         accumulate(c, pe);
         c->ev_pool.push_back(pe.a);
@@ -1854,11 +1843,6 @@ void drop_graphs(chhs_ctx* c) {
         if (c->graph[s]) (void)hipGraphDestroy(c->graph[s]);
         c->gexec[s] = nullptr;
         c->graph[s] = nullptr;
-        for (auto& pe : c->graph_pairs[s]) {
-            c->ev_pool.push_back(pe.a);
-            c->ev_pool.push_back(pe.b);
-        }
-        c->graph_pairs[s].clear();
     }
     for (auto& r : c->runs) {
         (void)hipGraphExecDestroy(r.exec);
@@ -1903,7 +1887,6 @@ hipGraphExec_t cycle_run(chhs_ctx* c, int n, int buf) {
 void ensure_graph(chhs_ctx* c, int slot, int buf) {
     if (!c->opts.use_graph || c->opts.timing != 0 || c->graph_failed || c->gexec[slot] != nullptr)
         return;
-    c->capturing = slot;
     const int saved_cur0 = c->cur[0];
     bool ok = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess;
     hipGraph_t g = nullptr;
@@ -1911,7 +1894,6 @@ void ensure_graph(chhs_ctx* c, int slot, int buf) {
         enqueue_cycle(c, true, buf);
         ok = hipStreamEndCapture(c->stream, &g) == hipSuccess && g != nullptr;
     }
-    c->capturing = -1;
     if (ok && hipGraphInstantiate(&c->gexec[slot], g, nullptr, nullptr, 0) != hipSuccess) {
         c->gexec[slot] = nullptr;
         ok = false;
@@ -2076,7 +2058,6 @@ int run_cycles(chhs_ctx* c, bool setup_pending = false) {
     c->last_cycles = 0;
     for (int i = 0; i < c->n_inst; ++i) c->last_cycles = std::max(c->last_cycles, c->hcyc[i]);
     HIP_TRY(hipStreamSynchronize(c->stream));
-    c->last_slot = -1;
     resolve_timing(c);
     return CHHS_OK;
 }
