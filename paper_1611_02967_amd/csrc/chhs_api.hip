@@ -1221,7 +1221,8 @@ template <typename T>
 void restore_copy0(chhs_ctx* c, const Hier<T>& H, int l) {
     for (int i = 0; i < c->n_inst; ++i) {
         const LevelDesc<T>& d = (*H.host)[size_t(i) * kMaxLevels + l];
-        if (d.u[1][0] == d.u[0][0] || d.n == 0) continue;
+        // an instance's tail levels are always on copy 0
+        if (d.u[1][0] == d.u[0][0] || d.n == 0 || l >= c->lay.info[i].tail) continue;
         const size_t nb = size_t(d.n) * sizeof(T);
         for (int k = 0; k < 3; ++k)
             (void)hipMemcpyAsync(d.u[0][k], d.u[1][k], nb, hipMemcpyDeviceToDevice, c->stream);

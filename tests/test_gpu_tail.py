@@ -113,3 +113,27 @@ def test_step_held_by_the_tail_stops_at_max_vcycles(chhs):
     assert rc == chhs.CHHS_E_NOCONV and st[0]["vcycles"] == 2 and st[0]["res_norm"] > 1e-10
     for x, y in zip(t, before):
         assert bool((x == y).all())
+
+
+@pytest.mark.parametrize("nu", [(3, 2), (2, 3)])
+@pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "mixed"])
+def test_odd_launches_on_a_level_leave_the_tails_of_other_instances_alone(chhs, nu, precision):
+    """A level that some instances smooth by an odd number of out-of-place
+    launches and others hold in their tail: every instance as alone, bit for bit."""
+    import torch
+    shapes = [(128, 128), (32, 32), (64, 64)]
+    phi0 = [uniform_field(s, 9400 + i, mean=0.1, amp=0.05) for i, s in enumerate(shapes)]
+
+    def run(idx):
+        probs = [chhs.make_problem(shapes[i], 1.0 / shapes[i][-1], 0.05, 2.0, 5e-4) for i in idx]
+        sv = chhs.Solver(probs, chhs.chhs_default_opts(nu1=nu[0], nu2=nu[1], precision=precision))
+        t = torch.from_numpy(np.concatenate([phi0[i].ravel() for i in idx])).to("cuda")
+        st = [t.clone(), t.clone(), torch.zeros_like(t), torch.zeros_like(t)]
+        _, stats = sv.step(*st, 2)
+        off = np.cumsum([0] + [phi0[i].size for i in idx])
+        return [[v.cpu().numpy()[off[k]:off[k + 1]] for v in st] + [stats[k]["vcycles"]]
+                for k in range(len(idx))]
+    batch = run([0, 1, 2])
+    for i in range(3):
+        for a, b in zip(batch[i], run([i])[0]):
+            assert np.array_equal(a, b), i
