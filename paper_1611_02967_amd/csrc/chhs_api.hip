@@ -1128,17 +1128,16 @@ Batch<float> batch32(chhs_ctx* c, int level, const int* active) {
     return make_batch(c->ddesc32, c->cur32, level, active);
 }
 
-// The hierarchy of one precision: device descriptors, host copies, current
-// copies of u per level.
+// The hierarchy of one precision: device descriptors, current copies of u per
+// level.
 template <typename T>
 struct Hier {
     const LevelDesc<T>* dev;
-    const std::vector<LevelDesc<T>>* host;
     int* cur;
 };
 
-Hier<double> hier64(chhs_ctx* c) { return {c->ddesc, &c->lay.desc, c->cur}; }
-Hier<float> hier32(chhs_ctx* c) { return {c->ddesc32, &c->lay.desc32, c->cur32}; }
+Hier<double> hier64(chhs_ctx* c) { return {c->ddesc, c->cur}; }
+Hier<float> hier32(chhs_ctx* c) { return {c->ddesc32, c->cur32}; }
 
 // Device results and flags with host mirror `buf`.
 chhs::InstResults results(chhs_ctx* c, int buf) {
@@ -1216,17 +1215,11 @@ void bricks(chhs_ctx* c, const Hier<T>& H, int l, int n, int last, const int* ac
 }
 
 // An odd number of out-of-place launches on level l left copy 1 current: copy
-// it back so that every level ends each V-cycle on copy 0.
+// it back, for the instances that took them (above their tail and in active),
+// so that every level ends each V-cycle on copy 0.
 template <typename T>
-void restore_copy0(chhs_ctx* c, const Hier<T>& H, int l) {
-    for (int i = 0; i < c->n_inst; ++i) {
-        const LevelDesc<T>& d = (*H.host)[size_t(i) * kMaxLevels + l];
-        // an instance's tail levels are always on copy 0
-        if (d.u[1][0] == d.u[0][0] || d.n == 0 || l >= c->lay.info[i].tail) continue;
-        const size_t nb = size_t(d.n) * sizeof(T);
-        for (int k = 0; k < 3; ++k)
-            (void)hipMemcpyAsync(d.u[0][k], d.u[1][k], nb, hipMemcpyDeviceToDevice, c->stream);
-    }
+void restore_copy0(chhs_ctx* c, const Hier<T>& H, int l, const int* active) {
+    chhs::launch_copy_back(make_batch(H.dev, H.cur, l, active), c->B[l].dev, c->B[l].n, c->stream);
     H.cur[l] = 0;
 }
 
@@ -1405,7 +1398,7 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int so
                                                   c->Bh[d].dev, c->Bh[d].n, color, c->stream);
                     }
         }
-        if (H.cur[d] != 0) restore_copy0(c, H, d);
+        if (H.cur[d] != 0) restore_copy0(c, H, d, act);
     }
 }
 
@@ -1486,7 +1479,7 @@ float time_level(chhs_ctx* c, const Hier<T>& H, int l, int reps, hipEvent_t ea, 
         *pre = std::min(*pre, m1);
         *post = std::min(*post, m2);
     }
-    if (H.cur[l] != 0) restore_copy0(c, H, l);
+    if (H.cur[l] != 0) restore_copy0(c, H, l, nullptr);
     return best;
 }
 
@@ -1520,7 +1513,7 @@ float time_level3(chhs_ctx* c, const Hier<T>& H, int l, int reps, hipEvent_t ea,
         if (hipEventElapsedTime(&ms, ea, eb) != hipSuccess) return -1.0f;
         best = std::min(best, ms);
     }
-    if (H.cur[l] != 0) restore_copy0(c, H, l);
+    if (H.cur[l] != 0) restore_copy0(c, H, l, nullptr);
     return best;
 }
 

@@ -193,6 +193,9 @@ void launch_prolong(int dim, const Batch<double>& b, const CellTask* t, int nt, 
                     hipStream_t st);
 void launch_prolong(int dim, const Batch<float>& b, const CellTask* t, int nt, bool bilinear,
                     hipStream_t st);
+// Copy 0 of u from copy 1 on level b.level of the active instances.
+void launch_copy_back(const Batch<double>& b, const CellTask* t, int nt, hipStream_t st);
+void launch_copy_back(const Batch<float>& b, const CellTask* t, int nt, hipStream_t st);
 // Mixed precision (finest level): a zero FP32 correction; the FP64 outer step
 // u' = u (+ e), R = f - N(u') written as u' (other FP64 copy), R and b = phi'
 // in FP32, and norm partials (as launch_residual_partials); an instance

@@ -498,6 +498,20 @@ __global__ __launch_bounds__(kBlock) void k_prolong(Batch<T> b, const CellTask* 
     F.p[idx] += C.p[c] - C.ub2[c];
 }
 
+// Copy 0 of u from copy 1, of the instances that took part in the cycle: an
+// instance that did not has nothing of this step in copy 1.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_copy_back(Batch<T> b, const CellTask* __restrict__ t) {
+    const CellTask tk = t[xcd_task()];
+    if (inactive(b.active, tk.inst)) return;
+    const Level<T> L = view_at(b, tk.inst, b.level, 1);
+    const int idx = tk.cell0 + threadIdx.x;
+    if (idx >= L.n) return;
+    L.phi_alt[idx] = L.phi[idx];
+    L.mu_alt[idx] = L.mu[idx];
+    L.p_alt[idx] = L.p[idx];
+}
+
 // ---- mixed precision: FP64 outer work around the FP32 correction solve ---------------
 
 // Zero correction on the FP32 finest level (current copy).
@@ -1119,6 +1133,12 @@ void launch_restrict_frozen(int dim, const Batch<double>& b, const CellTask* t, 
 void launch_restrict_frozen(int dim, const Batch<float>& b, const CellTask* t, int nt,
                             hipStream_t st) {
     CHHS_DISPATCH_T(dim, k_restrict_frozen, nt, b, t);
+}
+void launch_copy_back(const Batch<double>& b, const CellTask* t, int nt, hipStream_t st) {
+    if (nt > 0) hipLaunchKernelGGL(k_copy_back<double>, dim3(nt), dim3(kBlock), 0, st, b, t);
+}
+void launch_copy_back(const Batch<float>& b, const CellTask* t, int nt, hipStream_t st) {
+    if (nt > 0) hipLaunchKernelGGL(k_copy_back<float>, dim3(nt), dim3(kBlock), 0, st, b, t);
 }
 #undef CHHS_TARGS
 #define CHHS_TARGS double, false
