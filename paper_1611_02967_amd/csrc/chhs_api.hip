@@ -211,11 +211,13 @@ struct chhs_ctx {
     int cur[kMaxLevels] = {};       // current copy of u per FP64 level
     int cur32[kMaxLevels] = {};     // current copy of u per FP32 level
     bool fused_norm = false;
-    // p's mean is never subtracted by a launch of its own inside a step: the
+    // p's mean is not subtracted by a launch of its own after every cycle: the
     // equations hold p through differences only, and the copy to the caller's
     // arrays subtracts the mean that the last reduction found (res slot 4).
-    // Where the cycle's first finest-level launch can take a pending mean along
-    // as it loads p, it does
+    // The mean of the initial p, which may be large against p, is taken out
+    // before the first cycle smooths: by the cycle's first finest-level launch as
+    // it loads p (shift_in_cycle), by the tail that holds the finest level, or
+    // in the setup of a call's first step
     bool shift_in_cycle = false;
     bool loaded = false;
     // graph replay of one cycle; two slots in mixed precision (the FP64 finest
@@ -1348,7 +1350,8 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int so
                                               c->stream);
         chhs::launch_tail<T, !kPlain>(dim, H.dev, c->dinfo, c->tail_insts,
                                       int(c->lay.tail_insts.size()), act, 0u, cycle_shape(o),
-                                      c->lay.tail_lds, c->stream);
+                                      kPlain ? c->res : nullptr, c->cycles, c->lay.tail_lds,
+                                      c->stream);
     }
     const bool bil = o.prolong == 1;
     for (int d = depth - 1; d >= 0; --d) {
@@ -1743,6 +1746,12 @@ void enqueue_plain_cycle(chhs_ctx* c, bool count, int buf) {
 void apply_pshift(chhs_ctx* c) {
     chhs::launch_shift_p(batch(c, 0, nullptr), c->A[0].dev, c->A[0].n, c->res, c->stream);
     chhs::launch_clear_pshift(c->res, c->n_inst, c->stream);
+}
+
+// The cycles themselves take out the mean of the initial p (mixed precision
+// keeps it).
+bool mean_in_cycle(const chhs_ctx* c) {
+    return c->mixed || c->shift_in_cycle || c->lay.depth == 0;
 }
 
 // Mixed precision, one refinement step: zero FP32 correction, inner_cycles FP32
@@ -2187,8 +2196,9 @@ int step_loop(chhs_ctx* c, double* phi_prev, double* phi_cur, double* mu, double
     int rc = log != nullptr ? reserve_log(c, nsteps) : CHHS_OK;
     int done = 0;
     for (int m = 0; m < nsteps && rc == CHHS_OK; ++m) {
-        // the setup is not waited for; its norms come with the first cycle
-        rc = setup(c, phi_prev, phi_cur, mu, p, true, false);
+        // the setup is not waited for; its norms come with the first cycle (the
+        // p of a later step is the last one's, of mean zero)
+        rc = setup(c, phi_prev, phi_cur, mu, p, m > 0 || mean_in_cycle(c), false);
         if (rc) break;
         rc = run_cycles(c, true);
         if (rc) break;
@@ -2696,7 +2706,7 @@ int chhs_tune_sweeps(chhs_ctx* c, const double* phi_prev, const double* phi_cur,
         bool ok = true;
         for (int r = 0; r <= kTuneReps && ok; ++r) {
             const auto t0 = std::chrono::steady_clock::now();
-            int rc = setup(c, phi_prev, phi_cur, mu, p, true, false);
+            int rc = setup(c, phi_prev, phi_cur, mu, p, mean_in_cycle(c), false);
             if (rc == CHHS_OK) rc = run_cycles(c, true);
             const auto t1 = std::chrono::steady_clock::now();
             if (rc != CHHS_OK) return rc;

@@ -377,7 +377,7 @@ int prepare_tail(int dim, size_t lds_bytes);
 template <typename T, bool CORR>
 void launch_tail(int dim, const LevelDesc<T>* desc, const InstInfo* info, const int* insts,
                  int ninst, const int* active, unsigned cur_mask, const CycleShape& shape,
-                 size_t lds_bytes, hipStream_t st);
+                 const double* res, const int* cycles, size_t lds_bytes, hipStream_t st);
 
 // ---- the same with an owner thread per pair of cells (chhs_tail_own.hip) -----------
 // LDS of one tail level, in values: the records of u and one of zeros, the

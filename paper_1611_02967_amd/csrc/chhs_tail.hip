@@ -212,7 +212,9 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
                                                        const InstInfo* __restrict__ info,
                                                        const int* __restrict__ insts,
                                                        const int* __restrict__ active,
-                                                       unsigned cur_mask, CycleShape shape) {
+                                                       unsigned cur_mask, CycleShape shape,
+                                                       const double* __restrict__ res,
+                                                       const int* __restrict__ cycles) {
     extern __shared__ __align__(16) unsigned char tail_lds[];
     T* base = reinterpret_cast<T*>(tail_lds);
     const int inst = insts[blockIdx.x];
@@ -231,6 +233,9 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
         const T* g0 = top > 0 ? G.fr0 : G.f0;
         const T* g1 = top > 0 ? G.fr1 : G.f1;
         const T* g2 = top > 0 ? G.fr2 : G.f2;
+        // the mean of the initial p (a step's first cycle, the finest level here)
+        const T psh = !CORR && top == 0 && res != nullptr && cycles[inst] == 0
+                          ? T(res[inst * kResStride + 4]) : T(0);
         // Every global load of the first rounds is issued before any LDS
         // store, so the staging waits for memory once: two cells of the top
         // level per thread (the LDS budget keeps the top below 2 kTailThreads
@@ -268,7 +273,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
             if (idx < G.n) {
                 S.phi[idx] = tv[k][0];
                 S.mu[idx] = tv[k][1];
-                S.p[idx] = tv[k][2];
+                S.p[idx] = tv[k][2] - psh;
                 S.f0[idx] = tv[k][3];
                 S.f1[idx] = tv[k][4];
                 S.f2[idx] = tv[k][5];
@@ -289,7 +294,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const LevelDesc<T>* __res
         for (int idx = t0 + 2 * kTailThreads; idx < G.n; idx += blockDim.x) {
             S.phi[idx] = G.phi[idx];
             S.mu[idx] = G.mu[idx];
-            S.p[idx] = G.p[idx];
+            S.p[idx] = G.p[idx] - psh;
             S.f0[idx] = g0[idx];
             S.f1[idx] = g1[idx];
             S.f2[idx] = g2[idx];
@@ -403,23 +408,24 @@ int prepare_tail(int dim, size_t lds_bytes) {
 template <typename T, bool CORR>
 void launch_tail(int dim, const LevelDesc<T>* desc, const InstInfo* info, const int* insts,
                  int ninst, const int* active, unsigned cur_mask, const CycleShape& shape,
-                 size_t lds_bytes, hipStream_t st) {
+                 const double* res, const int* cycles, size_t lds_bytes, hipStream_t st) {
     if (ninst <= 0) return;
     if (dim == 2)
         hipLaunchKernelGGL((k_tail<2, T, CORR>), dim3(ninst), dim3(kTailThreads), lds_bytes, st,
-                           desc, info, insts, active, cur_mask, shape);
+                           desc, info, insts, active, cur_mask, shape, res, cycles);
     else
         hipLaunchKernelGGL((k_tail<3, T, CORR>), dim3(ninst), dim3(kTailThreads), lds_bytes, st,
-                           desc, info, insts, active, cur_mask, shape);
+                           desc, info, insts, active, cur_mask, shape, res, cycles);
 }
 
 template int prepare_tail<double, false>(int, size_t);
 template int prepare_tail<float, true>(int, size_t);
 template void launch_tail<double, false>(int, const LevelDesc<double>*, const InstInfo*,
                                          const int*, int, const int*, unsigned,
-                                         const CycleShape&, size_t, hipStream_t);
+                                         const CycleShape&, const double*, const int*, size_t,
+                                         hipStream_t);
 template void launch_tail<float, true>(int, const LevelDesc<float>*, const InstInfo*, const int*,
-                                       int, const int*, unsigned, const CycleShape&, size_t,
-                                       hipStream_t);
+                                       int, const int*, unsigned, const CycleShape&,
+                                       const double*, const int*, size_t, hipStream_t);
 
 }  // namespace chhs

@@ -272,6 +272,10 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
         return;
     }
     if (G.levels == 0) return;          // the instance's tail is worked by k_tail
+    // the mean of the initial p, taken out by a step's first cycle (the finest
+    // level here; later cycles carry what they add to it, of the size of p)
+    const T psh = !CORR && solve.out.cycles[inst] == 0 && G.finest != 0
+                      ? T(solve.out.res[inst * kResStride + 4]) : T(0);
     const bool owner = (own.fl >> kOwnValid) & 1u;
     const int my = owner ? int((own.fl >> kOwnLevel) & 7u) : -1;       // level below the tail's top one
     const int last = G.levels - 1;
@@ -334,7 +338,7 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
             if (my == 0 && live) {
                 P.u[c][0] = g[c][0];
                 P.u[c][1] = g[c][1];
-                P.u[c][2] = g[c][2];
+                P.u[c][2] = CORR ? g[c][2] : g[c][2] - psh;
                 P.f[c][0] = g[c][3];
                 P.f[c][1] = g[c][4];
                 P.f[c][2] = CORR ? g[c][5] : g[c][5] * cf.inv_lam;
