@@ -219,6 +219,8 @@ struct chhs_ctx {
     // it loads p (shift_in_cycle), by the tail that holds the finest level, or
     // in the setup of a call's first step
     bool shift_in_cycle = false;
+    bool p_pending = false;         // FP64: the level's p is to lose res slot 4 yet
+    bool defer_shift = false;       // chhs_get_solution subtracts res slot 4
     bool loaded = false;
     // graph replay of one cycle; two slots in mixed precision (the FP64 finest
     // level alternates its copy once per refinement step)
@@ -1746,6 +1748,13 @@ void enqueue_plain_cycle(chhs_ctx* c, bool count, int buf) {
 void apply_pshift(chhs_ctx* c) {
     chhs::launch_shift_p(batch(c, 0, nullptr), c->A[0].dev, c->A[0].n, c->res, c->stream);
     chhs::launch_clear_pshift(c->res, c->n_inst, c->stream);
+    c->p_pending = false;
+}
+
+// Before a call that reads or writes the level's fields: p as the last step
+// returned it.
+void settle_p(chhs_ctx* c) {
+    if (c->p_pending) apply_pshift(c);
 }
 
 // The cycles themselves take out the mean of the initial p (mixed precision
@@ -1959,6 +1968,7 @@ bool expect_more(const chhs_ctx* c, const std::vector<double>& rho) {
 // step is a schedule and nothing else).
 int run_cycles(chhs_ctx* c, bool setup_pending = false) {
     if (!setup_pending && !any_active(c)) return CHHS_OK;
+    c->p_pending = !c->mixed;
     for (int s = 0; s < 2; ++s)
         if (c->cycle_done[s] == nullptr && hipEventCreateWithFlags(&c->cycle_done[s],
                                                                     hipEventDisableTiming) != hipSuccess)
@@ -2109,6 +2119,7 @@ int setup(chhs_ctx* c, const double* phi_prev, const double* phi_cur, const doub
                                  c->n_inst, chhs::kReduceSetup, c->opts.tol,
                                  c->mixed ? 1 << 30 : c->opts.max_vcycles, c->stream);
     }
+    c->p_pending = !c->mixed;
     if (!defer) apply_pshift(c);
     int rc = check_launch();
     if (rc) return rc;
@@ -2446,7 +2457,9 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
     }
     // 3D plain FP64 with the fused step or bricks on the finest level: the first
     // pre-smoothing launch subtracts p's pending mean as it loads p
-    if (!c->mixed && (z3_at(c, 0) || c->lay.brick[0] > 0) && o->nu1 > 0) c->shift_in_cycle = true;
+    if (!c->mixed && z3_at(c, 0) && o->nu1 > 0) c->shift_in_cycle = true;
+    c->defer_shift = c->mixed || c->shift_in_cycle;
+    if (!c->mixed && c->lay.brick[0] > 0 && o->nu1 > 0) c->shift_in_cycle = true;
     {
         // the per-step log of chhs_step_log, reserved up front
         const size_t per_step = size_t(n_inst) * chhs::kResStride * sizeof(double);
@@ -2488,6 +2501,7 @@ int chhs_fas_vcycle(chhs_ctx* c, double* res_norm_host) {
 int chhs_residual_norms(chhs_ctx* c, double* out_host) {
     if (c == nullptr || out_host == nullptr) return CHHS_E_INVAL;
     if (!c->loaded) return CHHS_E_STATE;
+    settle_p(c);
     chhs::launch_residual_partials(c->dim, batch(c, 0, nullptr), c->A[0].dev, c->A[0].n,
                                    c->partial, c->stream);
     const double* src;
@@ -2496,6 +2510,8 @@ int chhs_residual_norms(chhs_ctx* c, double* out_host) {
     view_results(c, 0);
     chhs::launch_inst_reduce(src, rng, nullptr, nullptr, 0, c->dinfo, results(c, 0), c->n_inst,
                              chhs::kReduceQuery, c->opts.tol, 1 << 30, c->stream);
+    // the mean that this found is no pending one
+    if (!c->defer_shift) chhs::launch_clear_pshift(c->res, c->n_inst, c->stream);
     int rc = check_launch();
     if (rc) return rc;
     rc = sync_results(c);
@@ -2507,8 +2523,9 @@ int chhs_residual_norms(chhs_ctx* c, double* out_host) {
 int chhs_get_solution(chhs_ctx* c, double* phi, double* mu, double* p) {
     if (c == nullptr) return CHHS_E_INVAL;
     if (!c->loaded) return CHHS_E_STATE;
+    settle_p(c);
     Batch<double> b = batch(c, 0, nullptr);
-    b.pshift = c->res;
+    b.pshift = c->defer_shift ? c->res : nullptr;
     chhs::launch_get_solution(b, c->A[0].dev, c->A[0].n, c->dinfo, phi, mu, p, c->stream);
     return check_launch();
 }
@@ -2597,6 +2614,7 @@ int chhs_copy_field(chhs_ctx* c, int32_t level, int32_t field, double* dev, int3
     if (c == nullptr || dev == nullptr || c->n_inst != 1 || level < 0 ||
         level >= c->lay.info[0].nlev || field < 0 || field > 7 || (dir != 0 && dir != 1))
         return CHHS_E_INVAL;
+    if (level == 0) settle_p(c);
     const LevelDesc<double>& d = c->lay.desc[level];
     const int cu = c->cur[level];
     double* f[8] = {d.u[cu][0], d.u[cu][1], d.u[cu][2], d.f[0], d.f[1], d.f[2], d.pstar, d.psi};
@@ -2617,6 +2635,7 @@ int chhs_smooth(chhs_ctx* c, int32_t level, int32_t nsweeps) {
     // for the FP32 ones)
     if (tiled2d(c) && !c->lay.strip[level] && c->lay.tile_y[level] == chhs::kTileYTall)
         return CHHS_E_INVAL;
+    if (level == 0) settle_p(c);
     smooth_steps(c, level, nsweeps, nullptr, level == 0 ? CHHS_K_PRE0 : CHHS_K_COARSE);
     if (c->cur[level] != 0) {
         // the single instance's level: make the result copy 0 again
@@ -2635,6 +2654,7 @@ int chhs_smooth(chhs_ctx* c, int32_t level, int32_t nsweeps) {
 int chhs_restrict(chhs_ctx* c, int32_t level) {
     if (c == nullptr || c->n_inst != 1 || level < 0 || level + 1 >= c->lay.info[0].nlev)
         return CHHS_E_INVAL;
+    if (level == 0) settle_p(c);
     chhs::launch_restrict_residual(c->dim, batch(c, level, nullptr), c->A[level + 1].dev,
                                    c->A[level + 1].n, c->stream);
     chhs::launch_coarse_rhs(c->dim, batch(c, level, nullptr), c->A[level + 1].dev,

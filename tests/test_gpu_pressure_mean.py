@@ -1,5 +1,6 @@
 """GPU tests of the pressure's free constant: a step does not depend on the mean
-of the initial p, on every smoothing path.
+of the initial p, and the level's p that a program reads between calls is the
+one of mean zero, on every smoothing path.
 """
 import numpy as np
 import pytest
@@ -46,3 +47,31 @@ def test_step_from_a_pressure_with_a_large_mean(chhs, shape, opts, timing):
     assert a["total_vcycles"] == b["total_vcycles"]
     for x, y in zip(got, want):
         assert float((x - y).abs().max()) <= 1e-12
+
+
+@pytest.mark.parametrize("shape,opts", CASES)
+def test_level_pressure_after_a_step_has_mean_zero(chhs, shape, opts):
+    import torch
+    sv, t, _ = _step(chhs, shape, opts, 0.0, 1)
+    p = sv.read_field(0, "p")
+    assert abs(float(p.mean())) <= 1e-14
+    assert float((p - t[3]).abs().max()) <= 1e-15
+    sol = torch.empty_like(p)
+    sv.get_solution(p=sol)
+    assert float((sol - t[3]).abs().max()) <= 1e-15
+
+
+@pytest.mark.parametrize("shape", [(64, 64), (32, 32, 32)])
+def test_solution_holds_the_pressure_written_to_the_level(chhs, shape):
+    """Contexts whose cycles leave p's mean alone: a p written to the level comes
+    back as it is, also after the residual norms were asked for."""
+    import torch
+    opts = dict(order=1) if len(shape) == 2 else dict(smoother=3)
+    sv, t, _ = _step(chhs, shape, opts, 0.0, 1)
+    p = t[3] + 0.25
+    sv.write_field(0, "p", p)
+    sv.residual_norms()
+    sol = torch.empty_like(p)
+    sv.get_solution(p=sol)
+    assert bool((sol == p).all())
+    assert bool((sv.read_field(0, "p") == p).all())
