@@ -535,20 +535,24 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
             break;
         } else {
             if (!finest || solve.partial == nullptr) break;
-            if (my == 0) {
-                T n[3];
-                apply_n<DIM, T, CORR, 0>(P, U, cf, n);
-                double v[4] = {0.0, 0.0, 0.0, P.u[0][2] + P.u[1][2]};
-                auto add = [&](int c) {
-                    for (int k = 0; k < 3; ++k) {
-                        const T r = (k == 2 ? cf.lam : T(1)) * (P.f[c][k] - n[k]);
-                        v[k] += r * r;
-                    }
-                };
-                add(0);
-                __builtin_amdgcn_sched_barrier(0);      // one member at a time (registers)
-                apply_n<DIM, T, CORR, 1>(P, U, cf, n);
-                add(1);
+            // The waves of its owners whole: the lanes without a pair of it add zero.
+            if (tid < 64 * G.top_waves) {
+                double v[4] = {0.0, 0.0, 0.0, 0.0};
+                if (my == 0) {
+                    T n[3];
+                    apply_n<DIM, T, CORR, 0>(P, U, cf, n);
+                    v[3] = P.u[0][2] + P.u[1][2];
+                    auto add = [&](int c) {
+                        for (int k = 0; k < 3; ++k) {
+                            const T r = (k == 2 ? cf.lam : T(1)) * (P.f[c][k] - n[k]);
+                            v[k] += r * r;
+                        }
+                    };
+                    add(0);
+                    __builtin_amdgcn_sched_barrier(0);      // one member at a time (registers)
+                    apply_n<DIM, T, CORR, 1>(P, U, cf, n);
+                    add(1);
+                }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
