@@ -272,6 +272,13 @@ __device__ __forceinline__ void cell_apply(const Diffs<float>& q, float lam, flo
     n[2] = fma_of(lam, q.sp, (lam * gam) * q.samu);
 }
 
+// The combined residual norm from the three sums of squares and the cell volume,
+// rounded alike wherever the stopping test is made.
+__device__ __forceinline__ double combined_norm(const double* s, double hd) {
+#pragma clang fp contract(off)
+    return sqrt(__builtin_fma(s[2], hd, __builtin_fma(s[1], hd, s[0] * hd)));
+}
+
 // Cell-centred bi/trilinear interpolation of the coarse correction cv - cb at
 // fine cell (i, j, k) (coarse extents cnx, cny, cnz): along each axis 3/4 of
 // the parent and 1/4 of the parent's neighbour towards the cell, the parent

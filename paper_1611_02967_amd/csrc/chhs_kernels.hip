@@ -822,7 +822,7 @@ __global__ __launch_bounds__(kBlock) void k_inst_reduce(const double* __restrict
     double hd = in.h * in.h;
     if (in.dim == 3) hd *= in.h;
     const double a = s[0] * hd, bb = s[1] * hd, c = s[2] * hd;
-    const double tot = sqrt(a + bb + c);
+    const double tot = combined_norm(s, hd);
     const bool finite = tot == tot && tot < 1e300;
     const double o[6] = {sqrt(a), sqrt(bb), sqrt(c), tot, s[3] / double(in.n0), finite ? 0.0 : 1.0};
     for (int k = 0; k < 6; ++k) {

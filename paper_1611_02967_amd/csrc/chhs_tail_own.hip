@@ -573,7 +573,7 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
             // cycles up to the tolerance: the stopping test of k_inst_reduce
             const InstInfo& in = solve.info[inst];
             const double hd = in.dim == 3 ? in.h * in.h * in.h : in.h * in.h;
-            const double tot = sqrt((t[0] + t[1] + t[2]) * hd);
+            const double tot = combined_norm(t, hd);
             if (tot > solve.tol && tot < 1e300 && cycle < solve.cycles) continue;
             if (tid == 0) {
                 const double o[6] = {sqrt(t[0] * hd), sqrt(t[1] * hd), sqrt(t[2] * hd), tot,
