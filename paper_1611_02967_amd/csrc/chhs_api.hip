@@ -1263,7 +1263,8 @@ void smooth_steps(chhs_ctx* c, int l, int nsweeps, const int* active, int cls) {
 // launch also yields the fused norm partials; FP32: the correction form,
 // starting from a zero correction (zero_corr; the tiled finest level's first
 // launch then takes it as implied) or from the previous cycle's.  solve > 0
-// (whole_in_tail): the step's cycles, at most that many, results to mirror buf.
+// (whole_in_tail): the step's next cycles, at most that many, results to mirror
+// buf.
 bool zero_start(const chhs_ctx* c);
 
 template <typename T>
@@ -1344,8 +1345,8 @@ void enqueue_vcycle(chhs_ctx* c, const Hier<T>& H, bool zero_corr = true, int so
             tails = c->tails;
         else
             tails = c->tails32;
-        const chhs::TailSolve ts{kPlain && c->lay.tail_parts > 0 ? c->partial_t : nullptr, solve, o.tol,
-                                 c->dinfo, results(c, buf)};
+        const chhs::TailSolve ts{kPlain && c->lay.tail_parts > 0 ? c->partial_t : nullptr, solve,
+                                 o.max_vcycles, o.tol, c->dinfo, results(c, buf)};
         if (c->lay.own_threads > 0)
             chhs::launch_tail_own<T, !kPlain>(dim, tails, c->owners, c->n_inst, act, cycle_shape(o),
                                               ts, c->lay.own_threads, c->lay.own_lds,
@@ -1713,7 +1714,10 @@ void fold_cells(chhs_ctx* c, bool n_only, const int* act, const double** src, co
 }
 
 // Plain FP64, every instance's finest level held by the tail with owner threads:
-// one launch runs the counted cycles of a step (16^2: 333 -> 203 us a step).
+// one launch runs the counted cycles of a step (16^2: 333 -> 203 us a step), at
+// most kTailCycles of them, so that a launch ends within milliseconds (a V(2,2)
+// cycle takes at most 22 us) whatever max_vcycles is; the next one goes on.
+constexpr int kTailCycles = 128;
 bool whole_in_tail(const chhs_ctx* c) {
     return !c->mixed && c->lay.tail_parts == c->n_inst && c->opts.timing == 0;
 }
@@ -1721,7 +1725,7 @@ bool whole_in_tail(const chhs_ctx* c) {
 // Plain FP64: one V-cycle and the residual norms, read into mirror `buf`.
 void enqueue_plain_cycle(chhs_ctx* c, bool count, int buf) {
     if (count && whole_in_tail(c)) {
-        enqueue_vcycle(c, hier64(c), true, c->opts.max_vcycles, buf);
+        enqueue_vcycle(c, hier64(c), true, kTailCycles, buf);
         return;
     }
     const int* act = c->act;

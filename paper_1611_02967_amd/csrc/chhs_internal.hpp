@@ -435,11 +435,12 @@ struct TailDesc {
 };
 // Norm of a finest level held by the tail (FP64): partial (kNormStride doubles
 // at TailDesc::part) and, with cycles > 0, up to that many cycles in one launch,
-// an instance's until its norm is <= tol, its results written to out
-// (finest levels only, every instance).  partial null: no norm.
+// an instance's until its norm is <= tol or it has taken max_cycles in all, its
+// results and flags written to out (finest levels only, every instance).  partial
+// null: no norm.
 struct TailSolve {
     double* partial;
-    int cycles;
+    int cycles, max_cycles;
     double tol;
     const InstInfo* info;
     InstResults out;

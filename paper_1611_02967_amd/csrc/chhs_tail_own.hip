@@ -274,8 +274,9 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
     if (G.levels == 0) return;          // the instance's tail is worked by k_tail
     // the mean of the initial p, taken out by a step's first cycle (the finest
     // level here; later cycles carry what they add to it, of the size of p)
-    const T psh = !CORR && solve.out.cycles[inst] == 0 && G.finest != 0
-                      ? T(solve.out.res[inst * kResStride + 4]) : T(0);
+    const int before = CORR ? 0 : solve.out.cycles[inst];     // cycles of the step so far
+    const T mean = CORR ? T(0) : T(solve.out.res[inst * kResStride + 4]);
+    const T psh = before == 0 && G.finest != 0 ? mean : T(0);
     const bool owner = (own.fl >> kOwnValid) & 1u;
     const int my = owner ? int((own.fl >> kOwnLevel) & 7u) : -1;       // level below the tail's top one
     const int last = G.levels - 1;
@@ -570,15 +571,18 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
                         gstore(solve.partial, G.part * kNormStride + k, t[k]);
                 break;
             }
-            // cycles up to the tolerance: the stopping test of k_inst_reduce
+            // cycles up to the tolerance: the stopping test of k_inst_reduce; an
+            // instance that the launch leaves active goes on in the next one
             const InstInfo& in = solve.info[inst];
             const double hd = in.dim == 3 ? in.h * in.h * in.h : in.h * in.h;
             const double tot = combined_norm(t, hd);
-            if (tot > solve.tol && tot < 1e300 && cycle < solve.cycles) continue;
+            const bool more =
+                tot > solve.tol && tot < 1e300 && before + cycle < solve.max_cycles;
+            if (more && cycle < solve.cycles) continue;
             if (tid == 0) {
                 const double o[6] = {sqrt(t[0] * hd), sqrt(t[1] * hd), sqrt(t[2] * hd), tot,
                                      t[3] / double(in.n0), tot < 1e300 ? 0.0 : 1.0};
-                write_results(solve, inst, true, o, 0, cycle);
+                write_results(solve, inst, true, o, more ? 1 : 0, before + cycle);
             }
             break;
         }

@@ -17,7 +17,8 @@ def chhs():
     return binding
 
 
-@pytest.mark.parametrize("cycles", [1, 2, 5, 127])
+# at most 128 cycles a launch: the last one, one beyond, several launches
+@pytest.mark.parametrize("cycles", [1, 2, 5, 127, 128, 129, 300])
 def test_cycle_limit(chhs, cycles):
     """A tolerance below rounding is never met: every instance takes max_vcycles
     cycles, with the norms of a context that launches every cycle by itself (timed
