@@ -617,18 +617,22 @@ int step3_seg(const std::vector<int>& nxs, const std::vector<int>& nys, const st
 
 // Bricks of one 3D level over the listed instances (extents, -1 = skip) and
 // the steps per launch, 0 for no bricks.  A finest level is in bricks if no
-// instance has more than kBrickFinest cells there (by instance, as the sums of
-// the norm and of p's mean follow the bricks and a batched instance keeps the
-// bits of its single run); a coarse level if the batch has at most kBrickCoarse
-// cells there (larger launches are bound by throughput, and the per-color ones,
-// which give the same bits, recompute nothing).  Two steps while the bricks of
-// two steps (one workgroup per compute unit, by their LDS) are all resident at
-// once.  Two steps of the scheme, per-color launches / bricks: 16^3 928 / 583
-// us, 32^3 1509 / 903, 48 x 32 x 64 2020 / 1253, 64^3 (coarse levels) 2442 /
+// instance has more than kBrickFinest cells there and the batch at most
+// kBrickFinestAll, a coarse level if the batch has at most kBrickCoarse cells
+// there: larger launches are bound by throughput, and the per-color ones, which
+// give the same bits, recompute nothing (a finest level's sums of the norm and
+// of p's mean do follow the choice, in the last bits).  Two steps while the
+// bricks of two steps (one workgroup per compute unit, by their LDS) are all
+// resident at once.  Two steps of the scheme, per-color launches / bricks: 16^3
+// 928 / 583 us, 32^3 1509 / 903, 48 x 32 x 64 2020 / 1253, 64^3 (coarse levels) 2442 /
 // 1886, 64 grids of 16^3 1306 / 1195; beyond: 80^3 with its finest level per
 // color 2675 us, in bricks 2843, 8 grids of 64^3 6187 and 6588.  Mixed precision:
 // 32^3 1533 / 1047, 48 x 32 x 64 2062 / 1393, 64^3 2426 / 1880, 128^3 6783 / 6117.
-constexpr long kBrickFinest = 1L << 17, kBrickCoarse = 1L << 18;
+// Batches about kBrickFinestAll, the finest level per color / in bricks (with
+// coarse levels in bricks): 10 grids of 48^3 2930 / 3030 us, 14 3576 / 3856, 32 7489 /
+// 8741, 33 of 32^3 2645 / 2721, 128 8202 / 10165, 264 of 16^3 2011 / 1982, 384 2587 /
+// 2670; mixed precision, 10 of 48^3 2559 / 2842, 32 5915 / 7472, 33 of 32^3 2326 / 2455.
+constexpr long kBrickFinest = 1L << 17, kBrickFinestAll = 1L << 20, kBrickCoarse = 1L << 18;
 constexpr long kBrickTwo = 256;
 int brick_tasks(std::vector<BrickTask>& out, bool finest, const std::vector<int>& nxs,
                 const std::vector<int>& nys, const std::vector<int>& nzs) {
@@ -639,7 +643,7 @@ int brick_tasks(std::vector<BrickTask>& out, bool finest, const std::vector<int>
         total += n;
         if (n > (finest ? kBrickFinest : kBrickCoarse)) return 0;
     }
-    if (!finest && total > kBrickCoarse) return 0;
+    if (total > (finest ? kBrickFinestAll : kBrickCoarse)) return 0;
     const int tx = chhs::kBrickX, ty = chhs::kBrickY, tz = chhs::kBrickZ;
     for (size_t i = 0; i < nxs.size(); ++i) {
         if (nxs[i] < 0) continue;

@@ -1,4 +1,5 @@
-"""GPU test: FP64 smoothing in bricks has the bits of the per-color launches."""
+"""GPU tests: smoothing in bricks has the bits of the per-color launches, and batches
+on either side of the size up to which a finest level is in bricks agree."""
 import numpy as np
 import pytest
 
@@ -31,3 +32,22 @@ def test_one_vcycle_has_the_bits_of_the_per_color_launches(chhs, shape, nu, prol
         out.append([sv.read_field(0, n).cpu().numpy() for n in ("phi", "mu")])
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "mixed"])
+def test_batches_about_the_largest_in_bricks(chhs, precision):
+    """32 grids of 32^3 (2^20 cells) have their finest level in bricks, 33 smooth it
+    per color: the same updates, sums over the grid in another order (1e-13)."""
+    import torch
+    phi0 = [torch.from_numpy(uniform_field((32, 32, 32), 9750 + i, mean=0.1, amp=0.1).ravel()) for i in range(3)]
+    out = []
+    for count in (32, 33):
+        sv = chhs.Solver([chhs.make_problem((32, 32, 32), 1.0 / 32, 0.05, 2.0, 5e-4)] * count,
+                         chhs.chhs_default_opts(precision=precision))
+        phi = torch.cat([phi0[i % 3] for i in range(count)]).to("cuda")
+        t = [phi, phi.clone(), torch.zeros_like(phi), torch.zeros_like(phi)]
+        _, st = sv.step(*t, 1)
+        out.append([v[:3 * 32 ** 3] for v in t] + [[s["vcycles"] for s in st[:3]]])
+    assert out[0][4] == out[1][4]
+    for a, b in zip(out[0][:4], out[1][:4]):
+        assert float((a - b).abs().max()) <= 1e-13
