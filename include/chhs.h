@@ -81,7 +81,7 @@ typedef struct chhs_problem {
  * event pair delays the next launch by a few microseconds.  smoother selects
  * the 2D smoothing kernels of the levels above the single-workgroup tail:
  * 0 = default (LDS tiles; row-streaming strips on the finest level in mixed
- * precision, or when an instance has at least 3 2^20 cells), 1 = tiles
+ * precision, and for instances of at least 3 2^20 cells), 1 = tiles
  * everywhere (64 x 16 on the finest level), 2 = strips on every level (including
  * the explicit smoothing calls on tail levels).  On 3D levels above the tail:
  * 0 = the fused z-marching step on levels whose z segments hold at least 16
@@ -279,7 +279,8 @@ int chhs_level_shape(chhs_ctx* c, int32_t level, int32_t* nxyz3);
 /* The smoothing kernel the V-cycle uses on level `level` (counted from the
  * finest) of the batch: out3[0] = 0 square tiles (out3[1] = threads per block
  * of the pre-smoothing launches; the autotuner may give the post-smoothing
- * launches another block size), 1 row-streaming strips (out3[1] = rows per segment), 2 per-cell kernels (one
+ * launches another block size), 1 row-streaming strips (out3[1] = rows per segment;
+ * on the finest level the batch's smaller instances may be in tiles beside them), 2 per-cell kernels (one
  * launch per color; out3[1], out3[2] are those of such a launch also where small
  * 3D levels take the same steps in bricks of 8 x 4 x 4 cells), 3 inside the one-workgroup coarse tail for every instance
  * (out3[1] = 0), 4 fused 3D steps by z marching (out3[1] = planes per segment);

@@ -48,13 +48,13 @@ constexpr int kWideTiles = 256;
 // grid 537 us with 64 x 16 tiles on the finest level, 492 with 64 x 4).
 constexpr long kSmallTileLevel = 128;
 constexpr long kTinyTileLevel = 64;
-// FP64: the finest level is smoothed by row-streaming strips when an instance
-// has at least this many cells, by tiles otherwise: a strip's rows pass one
+// FP64: the finest level of an instance is smoothed by row-streaming strips when
+// it has at least this many cells, by tiles otherwise: a strip's rows pass one
 // after another, so short levels leave most of the device idle (one step,
 // strips against 512-thread tiles: 512^2 1178 / 924 us, 1024^2 1980 / 1729, 2048 x
 // 1024 2769 / 2420, 32 x 256^2 2222 / 1825, 2048^2 4128 / 4388).  By the instance
 // and not by the batch, so that an instance of a batch is smoothed as it is
-// alone.
+// alone: a batch with both takes a launch of each (Layout::both0).
 constexpr long kStripCells = 3L << 20;
 // Threads per tile block: the autotuned choice (256, 512 or 1024), else by
 // the number of tiles (FP64 launches of more tiles than compute units: 512, at
@@ -94,6 +94,8 @@ struct Layout {
     int brick[kMaxLevels] = {};
     std::vector<std::vector<BrickTask>> K;
     bool strip[kMaxLevels] = {};            // level smoothed by the row-streaming kernel
+    bool both0 = false;     // finest level: S[0] holds the large instances only, T[0] the others
+    int tile_parts0 = 0;    // their norm partials, which come before the strips'
     int tile_threads[kMaxLevels] = {};      // tiles: threads per block, 0 = by the tile count
     int tile_threads_post[kMaxLevels] = {}; // ... of the post-smoothing launches (0 = the same)
     int tile_y[kMaxLevels] = {};            // tile height of the level's tasks (T)
@@ -540,7 +542,21 @@ void task_ranges(std::vector<Range>& r, int n_inst, const std::vector<Task>& tas
 }
 
 void level0_ranges(Layout& L, int n_inst) {
-    if (L.strip[0])
+    if (L.both0) {
+        task_ranges(L.rngT0, n_inst, L.S[0]);
+        int at = 0;
+        for (int i = 0; i < n_inst; ++i) {
+            if (L.snx[0][i] < 0) continue;
+            Range& x = L.rngT0[i];
+            if (x.end > 0) {
+                x.begin += L.tile_parts0;
+                x.end += L.tile_parts0;
+            } else {
+                x = Range{at, at + tile_partials(L.snx[0][i], L.sny[0][i])};
+                at = x.end;
+            }
+        }
+    } else if (L.strip[0])
         task_ranges(L.rngT0, n_inst, L.S[0]);
     else if (!L.T[0].empty()) {
         L.rngT0.assign(n_inst, Range{0, 0});
@@ -892,9 +908,10 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         if (!mixed && in.tail == 0) L.tails[i].part = tail_part++;
     }
     // 2D smoother per level: row-streaming strips or square tiles (the same
-    // choice for the FP64 and the FP32 hierarchy)
-    long cells0 = 0;        // of the largest instance
-    for (int i = 0; i < n_inst; ++i) cells0 = std::max(cells0, long(L.info[i].n0));
+    // choice for the FP64 and the FP32 hierarchy); the finest FP64 level by instance
+    int large = 0, small = 0;
+    for (int i = 0; i < n_inst; ++i)
+        if (L.info[i].tail > 0) ++(L.info[i].n0 >= kStripCells ? large : small);
     if (dim == 2)
         for (int l = 0; l < kMaxLevels; ++l) {
             const int slots = strip_slots(l == 0 && !mixed, mixed);
@@ -917,9 +934,23 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
             L.strip[l] = even && o->order != 1 &&
                          (o->smoother == 2 ? !L.Sall[l].empty()
                                                    : (o->smoother == 0 && l == 0 && !L.T[l].empty() &&
-                                                      (mixed || cells0 >= kStripCells)));
+                                                      (mixed || large > 0)));
         }
     L.snx = lnx_t;
+    if (L.strip[0] && !mixed && o->smoother == 0 && small > 0) {
+        L.both0 = true;
+        std::vector<int> sx = lnx_t[0];
+        L.T[0].clear();
+        for (int i = 0; i < n_inst; ++i) {
+            if (sx[i] < 0 || L.info[i].n0 >= kStripCells) continue;
+            tile_tasks(L.T[0], i, sx[i], lny[0][i], L.tile_y[0], L.tile_parts0);
+            L.tile_parts0 += tile_partials(sx[i], lny[0][i]);
+            sx[i] = -1;
+        }
+        L.seg[0] = strip_seg(sx, lny[0], strip_slots(true, false));
+        L.S[0].clear();
+        strip_tasks(L.S[0], sx, lny[0], L.seg[0]);
+    }
     if (step3d_opts(dim, o))
         for (int l = 0; l < kMaxLevels; ++l) {
             L.zseg64[l] = step3_seg(lnx_t[l], lny[l], lnz[l], chhs::kStep3TX64, chhs::kStep3TY64);
@@ -982,7 +1013,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     fused_ranges(L, n_inst);
     L.partial_cap = int(std::max(L.A[0].size(), L.M0.size()));
     L.partial_t_cap =
-        L.tail_parts + int(std::max<size_t>(1, std::max({L.T[0].size(), L.cap_T[0], L.S[0].size(),
+        L.tail_parts + L.tile_parts0 + int(std::max<size_t>(1, std::max({L.T[0].size(), L.cap_T[0], L.S[0].size(),
                                                          L.cap_S[0], L.Z64[0].size(), L.K[0].size()})));
     L.off_desc = take(L.desc.size() * sizeof(LevelDesc<double>));
     L.off_desc32 = take(std::max<size_t>(1, L.desc32.size()) * sizeof(LevelDesc<float>));
@@ -1158,8 +1189,8 @@ double* level0_partials(chhs_ctx* c) {
 }
 
 // One 2D smoothing launch on level l (row-streaming strips or tiles, as
-// planned; all = every instance, else those whose tail starts below l);
-// flips the level's current copy.
+// planned, or on the finest level one of each; all = every instance, else those
+// whose tail starts below l); flips the level's current copy.
 template <typename T>
 void tiled(chhs_ctx* c, const Hier<T>& H, bool all, int l, int ns, int epi, bool pro,
            const int* active, int cls, bool rhs = false, const double* pshift = nullptr,
@@ -1172,8 +1203,11 @@ void tiled(chhs_ctx* c, const Hier<T>& H, bool all, int l, int ns, int epi, bool
         TimedScope t(c, cls);
         if (c->lay.strip[l]) {
             const Table<StripTask>& st = all ? c->Sall[l] : c->S[l];
-            chhs::launch_stream2d<T>(b, st.dev, st.n, level0, ns, epi, pro, zero, part, c->stream);
-        } else {
+            double* const sp = part != nullptr ? part + size_t(c->lay.tile_parts0) * chhs::kNormStride
+                                               : nullptr;
+            chhs::launch_stream2d<T>(b, st.dev, st.n, level0, ns, epi, pro, zero, sp, c->stream);
+        }
+        if (!c->lay.strip[l] || (l == 0 && c->lay.both0 && !all)) {
             const Table<TileTask>& tt = all ? c->Tall[l] : c->T[l];
             const int* thr = post && c->lay.tile_threads_post[l] > 0 ? c->lay.tile_threads_post
                                                                      : c->lay.tile_threads;
@@ -1575,6 +1609,13 @@ int autotune(chhs_ctx* c) {
     }
     const chhs_opts saved = c->opts;
     c->opts.timing = 0;
+    if (L.both0) {
+        // one kernel for every instance, the fastest: both tables are cut anew
+        L.both0 = false;
+        L.tile_parts0 = 0;
+        L.tile_y[0] = 0;
+        L.seg[0] = strip_seg(L.snx[0], L.sny[0], strip_slots(true, false));
+    }
     int rc = CHHS_OK;
     for (int l = 0; l < L.depth && rc == CHHS_OK; ++l) {
         if (c->T[l].n == 0) continue;
