@@ -115,6 +115,9 @@ def vcycle_bytes(dim, shape, level_kernels, sweeps=None):
                                     right-hand side of level l + 1 unless the
                                     tail forms it, 11/r; the prolongation
                                     (6 + 6/r)
+      per-cell levels in bricks   : (param = steps per launch, not 256) each launch
+                                    and the transfers as for fused 2D launches
+                                    of that many steps
       fused 3D steps ("zmarch")   : nu1 + nu2 launches of 88 B (72 B on the
                                     finest level, which reads no f_phi, f_p),
                                     the transfers as for per-cell kernels
@@ -133,6 +136,8 @@ def vcycle_bytes(dim, shape, level_kernels, sweeps=None):
     for s in shape:
         n0 *= s
     kinds = [k[0] if isinstance(k, (list, tuple)) else k for k in level_kernels]
+    params = [k[1] if isinstance(k, (list, tuple)) else 0 for k in level_kernels]
+    kinds = ["bricks" if k == "per-cell" and q in (1, 2) else k for k, q in zip(kinds, params)]
     total = 0.0
     for l, kind in enumerate(kinds):
         n = n0 / r ** l
@@ -142,7 +147,8 @@ def vcycle_bytes(dim, shape, level_kernels, sweeps=None):
             total += 8 * (9 * n + 2 * rest)
             break
         if kind in ("per-cell", "zmarch"):
-            next_tail = l + 1 < len(kinds) and kinds[l + 1] == "tail"
+            # the tail and bricks form their right-hand side themselves
+            next_tail = l + 1 < len(kinds) and kinds[l + 1] in ("tail", "bricks")
             smooth = ((a + b) * 2 * (44 if l == 0 else 52) / 8 if kind == "per-cell"
                       else (a + b) * (9 if l == 0 else 11))
             # the residual + restriction from the finest level of an instance
@@ -152,10 +158,11 @@ def vcycle_bytes(dim, shape, level_kernels, sweeps=None):
             v += 0 if next_tail else 11 / r
         else:
             read = 6 if l == 0 else 8
-            pre = -(-a // 2) * (read + 3) + 9 / r
+            steps = params[l] if kind == "bricks" else 2
+            pre = -(-a // steps) * (read + 3) + 9 / r
             if l > 0:
                 pre += 11 if kind == "strips" else 3
-            post = -(-b // 2) * (read + 3)
+            post = -(-b // steps) * (read + 3)
             post += (6 + 6 / r) if prolong == 1 else 6 / r
             v = pre + post
         total += 8 * v * n

@@ -281,8 +281,8 @@ int chhs_level_shape(chhs_ctx* c, int32_t level, int32_t* nxyz3);
  * of the pre-smoothing launches; the autotuner may give the post-smoothing
  * launches another block size), 1 row-streaming strips (out3[1] = rows per segment;
  * on the finest level the batch's smaller instances may be in tiles beside them), 2 per-cell kernels (one
- * launch per color; out3[1], out3[2] are those of such a launch also where small
- * 3D levels take the same steps in bricks of 8 x 4 x 4 cells), 3 inside the one-workgroup coarse tail for every instance
+ * launch per color, out3[1] = 256 threads per block; on small 3D levels the same
+ * steps in bricks of 8 x 4 x 4 cells, out3[1] = steps per launch, 1 or 2), 3 inside the one-workgroup coarse tail for every instance
  * (out3[1] = 0), 4 fused 3D steps by z marching (out3[1] = planes per segment);
  * out3[2] = blocks per launch (0 for the tail).  Reflects the autotuner's
  * choice.  Any batch size; CHHS_E_INVAL for a level no instance has. */

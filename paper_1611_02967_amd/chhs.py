@@ -242,7 +242,8 @@ KERNEL_KINDS = ["tiles", "strips", "per-cell", "tail", "zmarch"]
 
 
 def chhs_level_kernel(ctx, level):
-    """(kind, threads per block | rows per segment, blocks per launch) of a level."""
+    """(kind, threads per block | rows or planes per segment | steps per launch of
+    per-cell levels in bricks, blocks per launch) of a level."""
     out = (ctypes.c_int32 * 3)()
     _check(_lib.chhs_level_kernel(ctx, level, out), "chhs_level_kernel")
     return KERNEL_KINDS[out[0]], out[1], out[2]

@@ -2644,9 +2644,10 @@ int chhs_level_kernel(chhs_ctx* c, int32_t level, int32_t* out3) {
         out3[1] = c->mixed ? c->lay.zseg32[level] : c->lay.zseg64[level];
         out3[2] = c->mixed ? c->Z32[level].n : c->Z64[level].n;
     } else if (!tiled2d(c)) {
+        const int steps = c->lay.brick[level];
         out3[0] = 2;
-        out3[1] = chhs::kBlock;
-        out3[2] = c->Bh[level].n;
+        out3[1] = steps > 0 ? steps : chhs::kBlock;
+        out3[2] = steps > 0 ? c->K[level].n : c->Bh[level].n;
     } else if (c->lay.strip[level]) {
         out3[0] = 1;
         out3[1] = c->lay.seg[level];
