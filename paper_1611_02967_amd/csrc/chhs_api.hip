@@ -234,6 +234,7 @@ struct chhs_ctx {
     std::vector<Run> runs;
     int last_cycles = 0;            // cycles of the last step (the slowest instance's)
     bool graph_failed = false;
+    bool runs_failed = false;       // a graph of several cycles could not be captured
     // kernel timing (opts.timing)
     struct Pending { hipEvent_t a, b; int cls; };
     std::vector<hipEvent_t> ev_pool;
@@ -1918,7 +1919,8 @@ void drop_graphs(chhs_ctx* c) {
 constexpr int kCycleRuns[] = {16, 12, 8, 6, 4, 3, 2};
 
 // The graph of n counted cycles from the current copy, results to mirror buf;
-// null when it cannot be captured (the caller then replays single cycles).
+// null when it cannot be captured (the caller then replays single cycles, in later
+// steps too).
 hipGraphExec_t cycle_run(chhs_ctx* c, int n, int buf) {
     const int copy = c->mixed ? c->cur[0] : 0;
     for (const auto& r : c->runs)
@@ -1935,6 +1937,7 @@ hipGraphExec_t cycle_run(chhs_ctx* c, int n, int buf) {
     (void)hipGetLastError();
     if (!ok) {
         if (r.graph) (void)hipGraphDestroy(r.graph);
+        c->runs_failed = true;
         return nullptr;
     }
     c->runs.push_back(r);
@@ -2044,7 +2047,7 @@ int run_cycles(chhs_ctx* c, bool setup_pending = false) {
     auto launch = [&](int n) -> int {
         Flight f{next, launches++ & 1, 1, c->pending.size()};
         hipGraphExec_t run = nullptr;
-        if (graphs && n > 1) {
+        if (graphs && n > 1 && !c->runs_failed) {
             // a mixed single step reads back into the mirror of the copy it
             // starts from: this run takes the other one than its successor
             if (c->mixed) f.mirror = (c->cur[0] ^ (n & 1)) ^ 1;
