@@ -425,7 +425,7 @@ void tail_owners(int dim, int top, int nlev, int order, const LevelDesc<T>* desc
             o.fl = (1u << chhs::kOwnValid) | (both ? 1u << chhs::kOwnMid : 0u) |
                    (red ? 1u << chhs::kOwnRed : 0u) | (lead ? 1u << chhs::kOwnFirst : 0u) |
                    (unsigned(l - top) << chhs::kOwnLevel);
-            if (corr && dim == 2 && l + 1 == nlev && nx % 2 == 0 && D.n <= 128)
+            if (corr && dim == 2 && l + 1 == nlev && nx % 2 == 0)
                 o.fl |= 1u << chhs::kOwnKapFirst;
             for (int c = 0; c < 2; ++c) {
                 const int e = c ^ red;

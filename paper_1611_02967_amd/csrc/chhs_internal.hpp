@@ -409,8 +409,8 @@ constexpr int kOwnRed = 13;     // the red member is the right one
 constexpr int kOwnFirst = 14;   // first pair of its coarse cell
 constexpr int kOwnValid = 15;   // the thread owns a pair
 constexpr int kOwnLevel = 16;
-// 2D correction form, an even coarsest grid of at most 128 cells: kap nF is
-// rounded before it is added to chi', as k_tail does there
+// 2D correction form, a coarsest grid of even x extent: kap nF is rounded before
+// it is added to chi', as k_tail rounds it there
 constexpr int kOwnKapFirst = 19;
 struct TailOwner {
     unsigned fl;
