@@ -759,11 +759,11 @@ _CSRC = "paper_1611_02967_amd/csrc/"
 TRAFFIC_KERNELS = [
     ("refine", r"k_mixed_residual_rows", 100.0, ["chhs_refine2d.hip", "chhs_cell.hpp"]),
     ("pre0", r"k_tile2d<float, \w+, 2, 1, false, true, \d+, false, \d+, true>", 46.0,
-     ["chhs_tile2d.hip", "chhs_cell.hpp", "chhs_internal.hpp"]),
+     ["chhs_tile2d.hpp", "chhs_tile2d_f32.hip", "chhs_cell.hpp", "chhs_internal.hpp"]),
     ("pre0", r"k_tile2d<float, \w+, 2, 1, false, true, \d+, false, \d+, false>", 58.0,
-     ["chhs_tile2d.hip", "chhs_cell.hpp", "chhs_internal.hpp"]),
+     ["chhs_tile2d.hpp", "chhs_tile2d_f32.hip", "chhs_cell.hpp", "chhs_internal.hpp"]),
     ("post0", r"k_tile2d<float, \w+, 2, 0, true, true, \d+, false, \d+, false>", 54.0,
-     ["chhs_tile2d.hip", "chhs_cell.hpp", "chhs_internal.hpp"]),
+     ["chhs_tile2d.hpp", "chhs_tile2d_f32.hip", "chhs_cell.hpp", "chhs_internal.hpp"]),
     ("pre0", r"k_stream2d<double, true, 2, 1,", 90.0,
      ["chhs_stream2d.hip", "chhs_cell.hpp", "chhs_internal.hpp"]),
     ("post0", r"k_stream2d<double, true, 2, 2,", 84.0,

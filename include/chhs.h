@@ -85,13 +85,16 @@ typedef struct chhs_problem {
  * everywhere (64 x 16 on the finest level), 2 = strips on every level (including
  * the explicit smoothing calls on tail levels).  On 3D levels above the tail:
  * 0 = the fused z-marching step on levels whose z segments hold at least 16
- * planes, per-cell red-black kernels (one launch per color) on the others,
+ * planes, per-cell red-black updates on the others (in bricks of 8 x 4 x 4 cells
+ * on small levels, one launch per color on larger ones, with the same bits),
  * 3 = per-cell kernels on every level, 4 = the fused step on every level
  * (3D second-order scheme only).  All kernels perform the same red-black
  * updates (results agree to rounding).
  * tile_threads = 0 (default) gives tiled levels 1024-thread blocks when they
  * have at most 256 tiles, otherwise 512-thread (FP64) or 256-thread ones; 256, 512 or 1024
- * fixes the block size of every tiled level (the same arithmetic per cell).
+ * fixes the block size of every tiled level (the same arithmetic per cell); the
+ * FP64 kernel that 1024 stands for has a thread for every pair of cells that a
+ * tile depends on, 320 to 960 of them by the tile's height and halo.
  * tile_rows = 0 (default) cuts tiled levels into 64 x 8 tiles when they have at
  * most 128 tiles of 64 x 16 (over the batch; FP64 ones of at most 64 into 64 x 4)
  * and into 64 x 16 tiles otherwise (in mixed precision, or with smoother = 1,
@@ -106,8 +109,8 @@ typedef struct chhs_problem {
  * 4 rows, but on the FP32 finest level with 16; there also 64 x 32 tiles of
  * 512 and 1024 threads; the pre- and post-smoothing launches of a tile
  * height each take their fastest block size) and strips of 1/4, 1/2, 1, 2
- * and 4 times the default segment height.  3D: the fused step or the
- * per-cell kernels.
+ * and 4 times the default segment height.  3D: the fused step or one launch per
+ * color (levels in bricks keep them).
  * order = 2 (default; 0 means the same) solves the second-order scheme
  * (2.4)-(2.7).  order = 1 solves instead the first-order convex-splitting step
  * that Remark 2.2 names as a way to obtain phi^1 from phi^0 (its form is cited,

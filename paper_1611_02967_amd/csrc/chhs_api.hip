@@ -3,8 +3,8 @@
 // Owns the multigrid hierarchies of a batch of independent instances carved
 // out of the caller's workspace, the task tables that let one launch per level
 // cover every instance, the FAS V-cycle schedule (optionally replayed as a
-// captured HIP graph), the per-instance stopping test (one small readback per
-// cycle), the mixed-precision iterative refinement, and the time-step loop
+// captured HIP graph), the per-instance stopping test (a small pinned
+// mirror that each cycle's reduction writes), the mixed-precision iterative refinement, and the time-step loop
 // with its state rotation.
 #include <algorithm>
 #include <chrono>
@@ -641,10 +641,11 @@ int step3_seg(const std::vector<int>& nxs, const std::vector<int>& nys, const st
 // of p's mean do follow the choice, in the last bits).  Two steps while the
 // bricks of two steps (one workgroup per compute unit, by their LDS) are all
 // resident at once.  Two steps of the scheme, per-color launches / bricks: 16^3
-// 928 / 583 us, 32^3 1509 / 903, 48 x 32 x 64 2020 / 1253, 64^3 (coarse levels) 2442 /
-// 1886, 64 grids of 16^3 1306 / 1195; beyond: 80^3 with its finest level per
-// color 2675 us, in bricks 2843, 8 grids of 64^3 6187 and 6588.  Mixed precision:
-// 32^3 1533 / 1047, 48 x 32 x 64 2062 / 1393, 64^3 2426 / 1880, 128^3 6783 / 6117.
+// 971 / 631 us, 32^3 1565 / 949, 48 x 32 x 64 2100 / 1300, the coarse levels of 64^3
+// 2583 / 2040 and of 128^3 7670 / 7035, 64 grids of 16^3 1582 / 1358; beyond: 80^3 with
+// its finest level per color 2675 us, in bricks 2843, 8 grids of 64^3 6187 and
+// 6588.  Mixed precision: 32^3 1571 / 1087, 48 x 32 x 64 2091 / 1420, 64^3 2615 / 1990,
+// 128^3 6836 / 6120.
 // Batches about kBrickFinestAll, the finest level per color / in bricks (with
 // coarse levels in bricks): 10 grids of 48^3 2930 / 3030 us, 14 3576 / 3856, 32 7489 /
 // 8741, 33 of 32^3 2645 / 2721, 128 8202 / 10165, 264 of 16^3 2011 / 1982, 384 2587 /
@@ -1563,7 +1564,10 @@ float time_level3(chhs_ctx* c, const Hier<T>& H, int l, int reps, hipEvent_t ea,
 }
 
 // 3D: per level above the tail, the fused step or one launch per color,
-// whichever smooths faster on the problem at hand.
+// whichever smooths faster on the problem at hand.  Levels in bricks keep them:
+// where the rule takes bricks, both others are slower (two steps, bricks / per
+// color / fused everywhere: 16^3 630 / 874 / 1754 us, 48^3 1402 / 2041 / 4776, 8 grids of
+// 48^3 4435 / 4808 / 7525; mixed 1489 / 1994 / 4272 at 48^3).
 int autotune3(chhs_ctx* c) {
     hipEvent_t ea = nullptr, eb = nullptr;
     if (hipEventCreate(&ea) != hipSuccess || hipEventCreate(&eb) != hipSuccess) {
@@ -2481,8 +2485,7 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
                        hipMemcpyHostToDevice, st) != hipSuccess)
         rc = CHHS_E_HIP;
     if (rc) return fail(CHHS_E_HIP);
-    // pinned mirror, same layout as the device result block: res | act_next |
-    // cycles, then the energies
+    // pinned mirror: res of all instances | act | cycles, then the energies
     const size_t nres = size_t(n_inst) * chhs::kResStride;
     const size_t nint = (2 * size_t(n_inst) * sizeof(int) + sizeof(double) - 1) / sizeof(double);
     const size_t hbytes = (2 * nres + nint) * sizeof(double);

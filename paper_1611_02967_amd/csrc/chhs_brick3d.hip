@@ -27,8 +27,8 @@
 // with all loads issued at once and phases at LDS latency.  The recomputation
 // around small bricks costs little while the level does not fill the device, and
 // 8 x 4 x 4 gives the most workgroups whose slots still fit one per thread.
-// Measured, per-color launches / bricks: two steps of 32^3 1509 / 903 us, of 48 x
-// 32 x 64 2020 / 1253, of 128^3 (its three coarse levels) 7693 / 7034.
+// Measured, per-color launches / bricks: two steps of 32^3 1565 / 949 us, of 48 x
+// 32 x 64 2100 / 1300, of 128^3 (its three coarse levels) 7670 / 7035.
 //
 // A slot is a pair of x-adjacent cells (x even) within H faces of the brick;
 // every slot has its own thread.  Slots are ordered by their distance from the

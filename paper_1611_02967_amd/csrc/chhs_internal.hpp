@@ -288,14 +288,14 @@ constexpr int kTileYTiny = 4;
 constexpr int kTileYTall = 32;
 // ns fused smoothing steps on level b.level of every tasked instance, read from
 // copy b.cur and written to the other copy; epi 0 none, 1 residual + restriction
-// into level + 1 (copy b.cur_c), 2 residual-norm partials (4 per block, in task
-// order); pro: prolongation of level + 1's correction first; level0: f_phi =
+// into level + 1 (copy b.cur_c), 2 residual-norm partials (kNormStride doubles per
+// 64 x 4 cells, from TileTask::part); pro: prolongation of level + 1's correction first; level0: f_phi =
 // phi^m and f_p = 0 implied; threads: 256, 512 or 1024 per block (four, two
 // or one pair of cells per thread; FP64 with 1024: k_block2d, a thread for each
 // pair within the halo's faces, even extents only);
 // rhs: first pre-smoothing launch on a coarse level, which first forms the FAS
 // right-hand side f += N(u) (not with level0, pro or epi 2); ty: tile height,
-// kTileY or (not with level0) kTileYSmall or kTileYTiny, as the tasks were cut,
+// kTileY, kTileYSmall or kTileYTiny (the last two not with zero), as the tasks were cut,
 // or (FP32, not with rhs) kTileYTall;
 // zero (FP32 only, the finest level's first launch of a correction cycle, 64 x
 // 16 or 64 x 32 tiles, not with pro, rhs or epi 2): u is taken as zero instead of read.
