@@ -114,7 +114,7 @@ struct Layout {
     size_t own_lds = 0;
     int tail_parts = 0;         // instances whose finest level is there (FP64): their norm
                                 // partials come first in partial_t
-    std::vector<TailOwner> owners;
+    std::vector<std::pair<int, std::vector<TailOwner>>> owners;     // of one instance per kind of tail
     std::vector<TailDesc<double>> tails;
     std::vector<TailDesc<float>> tails32;
     std::vector<int> tail_insts;
@@ -354,9 +354,9 @@ int own_threads(const std::vector<int>& ext, int top) {
 }
 
 // The owner threads of one instance's tail (own: one entry per thread, all
-// zero on entry) and the description of its levels.  desc: the instance's
-// levels, their phi_* and phi^m in one workspace (close together: the tail's
-// levels are small and allocated one after another).
+// zero on entry; null: not wanted) and the description of its levels.  desc: the
+// instance's levels, their phi_* and phi^m in one workspace (close together: the
+// tail's levels are small and allocated one after another).
 template <typename T>
 void tail_owners(int dim, int top, int nlev, int order, const LevelDesc<T>* desc, TailOwner* own,
                  TailDesc<T>& d) {
@@ -391,7 +391,7 @@ void tail_owners(int dim, int top, int nlev, int order, const LevelDesc<T>* desc
             prev_wave = -1;
         }
         const int hx = (nx + 1) / 2;
-        for (int q = 0; q < np; ++q) {
+        for (int q = 0; own != nullptr && q < np; ++q) {
             // above the coarsest level the pairs of one coarse cell are
             // 2^(dim - 1) consecutive threads
             int m, j, k = 0;
@@ -440,6 +440,20 @@ void tail_owners(int dim, int top, int nlev, int order, const LevelDesc<T>* desc
         t += np;
         off += chhs::own_words(D.n, corr);
     }
+}
+
+// Two instances' tails have the same owner threads: equal extents, and their
+// phi_* and phi^m at equal distances.
+template <typename T>
+bool same_tail(const LevelDesc<T>* a, int ta, int na, const LevelDesc<T>* b, int tb, int nb) {
+    if (na - ta != nb - tb) return false;
+    for (int l = 0; l < na - ta; ++l) {
+        const LevelDesc<T>&x = a[ta + l], &y = b[tb + l];
+        if (x.nx != y.nx || x.ny != y.ny || x.nz != y.nz || x.pstar - a[ta].pstar != y.pstar - b[tb].pstar ||
+            x.psi - a[ta].psi != y.psi - b[tb].psi)
+            return false;
+    }
+    return true;
 }
 
 void cell_tasks(std::vector<CellTask>& out, int inst, int n) {
@@ -892,23 +906,37 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
         if (!in.fused && mixed && dim == 3 && step3d_opts(dim, o)) cell_tasks(L.A0x, i, cells[0]);
         if (tail == 0) cell_tasks(L.A0t, i, cells[0]);
     }
-    // the owner threads and levels of the tails
-    L.owners.assign(size_t(n_inst) * L.own_threads, TailOwner{});
-    L.tails.assign(mixed ? 0 : n_inst, TailDesc<double>{});
-    L.tails32.assign(mixed ? n_inst : 0, TailDesc<float>{});
+    // the levels of the tails, and the owner threads of one instance per kind of
+    // tail (made and sent for every instance they were most of a batch's setup:
+    // 512 grids of 16^2 2050 us, 530 so)
     int tail_part = 0;
-    for (int i = 0; base != nullptr && i < n_inst; ++i) {
-        if (!L.own[i]) continue;
-        TailOwner* own = &L.owners[size_t(i) * L.own_threads];
-        const InstInfo& in = L.info[i];
-        if (mixed)
-            tail_owners(dim, in.tail, in.nlev, in.order, &L.desc32[size_t(i) * kMaxLevels], own,
-                        L.tails32[i]);
-        else
-            tail_owners(dim, in.tail, in.nlev, in.order, &L.desc[size_t(i) * kMaxLevels], own,
-                        L.tails[i]);
-        if (!mixed && in.tail == 0) L.tails[i].part = tail_part++;
-    }
+    auto describe = [&](auto& tails, const auto& desc) {
+        tails.resize(n_inst);
+        for (int i = 0; i < n_inst; ++i) {
+            if (!L.own[i]) continue;
+            const InstInfo& in = L.info[i];
+            const auto* d = &desc[size_t(i) * kMaxLevels];
+            int from = i;
+            for (const auto& k : L.owners)
+                if (same_tail(d, in.tail, in.nlev, &desc[size_t(k.first) * kMaxLevels],
+                              L.info[k.first].tail, L.info[k.first].nlev)) {
+                    from = k.first;
+                    break;
+                }
+            TailOwner* own = nullptr;
+            if (from == i) {
+                L.owners.push_back({i, std::vector<TailOwner>(L.own_threads, TailOwner{})});
+                own = L.owners.back().second.data();
+            }
+            tail_owners(dim, in.tail, in.nlev, in.order, d, own, tails[i]);
+            tails[i].own_from = from;
+            if (!mixed && in.tail == 0) tails[i].part = tail_part++;
+        }
+    };
+    if (base != nullptr && mixed)
+        describe(L.tails32, L.desc32);
+    else if (base != nullptr)
+        describe(L.tails, L.desc);
     // 2D smoother per level: row-streaming strips or square tiles (the same
     // choice for the FP64 and the FP32 hierarchy); the finest FP64 level by instance
     int large = 0, small = 0;
@@ -1021,7 +1049,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
     L.off_desc32 = take(std::max<size_t>(1, L.desc32.size()) * sizeof(LevelDesc<float>));
     L.off_info = take(L.info.size() * sizeof(InstInfo));
     L.off_tail = take(L.tail_insts.size() * sizeof(int));
-    L.off_owners = take(L.owners.size() * sizeof(TailOwner));
+    L.off_owners = take(size_t(n_inst) * L.own_threads * sizeof(TailOwner));
     L.off_tails = take(n_inst * sizeof(TailDesc<double>));
     L.off_rngA0 = take(n_inst * sizeof(Range));
     L.off_rngT0 = take(n_inst * sizeof(Range));
@@ -2430,15 +2458,15 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
                        hipMemcpyHostToDevice, st) != hipSuccess ||
         hipMemcpyAsync(c->dinfo, L.info.data(), L.info.size() * sizeof(InstInfo),
                        hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(c->tail_insts, L.tail_insts.data(), L.tail_insts.size() * sizeof(int),
-                       hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(c->owners, L.owners.data(), L.owners.size() * sizeof(TailOwner),
-                       hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(c->tails,
-                       c->mixed ? static_cast<const void*>(L.tails32.data())
-                                : static_cast<const void*>(L.tails.data()),
-                       n_inst * (c->mixed ? sizeof(TailDesc<float>) : sizeof(TailDesc<double>)),
-                       hipMemcpyHostToDevice, st) != hipSuccess ||
+        (!L.tail_insts.empty() &&
+         hipMemcpyAsync(c->tail_insts, L.tail_insts.data(), L.tail_insts.size() * sizeof(int),
+                        hipMemcpyHostToDevice, st) != hipSuccess) ||
+        (L.own_threads > 0 &&
+         hipMemcpyAsync(c->tails,
+                        c->mixed ? static_cast<const void*>(L.tails32.data())
+                                 : static_cast<const void*>(L.tails.data()),
+                        n_inst * (c->mixed ? sizeof(TailDesc<float>) : sizeof(TailDesc<double>)),
+                        hipMemcpyHostToDevice, st) != hipSuccess) ||
         hipMemcpyAsync(c->rngA0, L.rngA0.data(), n_inst * sizeof(Range), hipMemcpyHostToDevice,
                        st) != hipSuccess ||
         hipMemcpyAsync(c->rngT0, L.rngT0.data(), n_inst * sizeof(Range), hipMemcpyHostToDevice,
@@ -2464,6 +2492,17 @@ int chhs_init(const chhs_problem* p, int32_t n_inst, const chhs_opts* o, void* w
         rc |= upload(c->ZR32[l], b, L.off_ZR32[l], L.ZR32[l], st);
         rc |= upload(c->BcS[l], b, L.off_BcS[l], L.BcS[l], st);
         rc |= upload(c->K[l], b, L.off_K[l], L.K[l], st);
+    }
+    for (const auto& k : L.owners)
+        if (hipMemcpyAsync(c->owners + size_t(k.first) * L.own_threads, k.second.data(),
+                           k.second.size() * sizeof(TailOwner), hipMemcpyHostToDevice, st) != hipSuccess)
+            rc = CHHS_E_HIP;
+    if (int(L.owners.size()) < n_inst && L.own_threads > 0) {
+        if (c->mixed)
+            chhs::launch_spread_owners(c->tails32, c->owners, n_inst, L.own_threads, st);
+        else
+            chhs::launch_spread_owners(c->tails, c->owners, n_inst, L.own_threads, st);
+        rc |= check_launch();
     }
     rc |= upload(c->A0n, b, L.off_A0n, L.A0n, st);
     rc |= upload(c->A0t, b, L.off_A0t, L.A0t, st);

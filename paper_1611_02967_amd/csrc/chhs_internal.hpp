@@ -432,7 +432,12 @@ struct TailDesc {
     int levels, finest, cubic;     // levels 0: the instance is not worked here
     unsigned single, joined;
     int top_waves, part;           // waves of the top level's owners; its norm partial (finest level)
+    int own_from;                  // instance of the same tail whose owner threads it copies, or itself
 };
+// owners of instance i <- those of instance TailDesc::own_from, [ninst][threads]
+template <typename T>
+void launch_spread_owners(const TailDesc<T>* tails, TailOwner* owners, int ninst, int threads,
+                          hipStream_t st);
 // Norm of a finest level held by the tail (FP64): partial (kNormStride doubles
 // at TailDesc::part) and, with cycles > 0, up to that many cycles in one launch,
 // an instance's until its norm is <= tol or it has taken max_cycles in all, its

@@ -595,6 +595,13 @@ __global__ __launch_bounds__(NT) void k_tail_own(const TailDesc<T>* __restrict__
                 for (int k = 0; k < 3; ++k) gstore(G.u[k], P.cell(c), P.u[c][k]);
 }
 
+template <typename T>
+__global__ void k_spread_owners(const TailDesc<T>* __restrict__ tails, TailOwner* owners) {
+    const int inst = blockIdx.x, from = tails[inst].own_from;
+    if (tails[inst].levels == 0 || from == inst) return;
+    owners[inst * blockDim.x + threadIdx.x] = owners[from * blockDim.x + threadIdx.x];
+}
+
 }  // namespace
 
 namespace {
@@ -632,6 +639,14 @@ void launch_tail_own(int dim, const TailDesc<T>* tails, const TailOwner* owners,
                        st, tails, owners, threads, active, shape, solve);
 }
 
+template <typename T>
+void launch_spread_owners(const TailDesc<T>* tails, TailOwner* owners, int ninst, int threads,
+                          hipStream_t st) {
+    hipLaunchKernelGGL(k_spread_owners<T>, dim3(ninst), dim3(threads), 0, st, tails, owners);
+}
+
+template void launch_spread_owners<double>(const TailDesc<double>*, TailOwner*, int, int, hipStream_t);
+template void launch_spread_owners<float>(const TailDesc<float>*, TailOwner*, int, int, hipStream_t);
 template int prepare_tail_own<double, false>(int, int, size_t);
 template int prepare_tail_own<float, true>(int, int, size_t);
 template void launch_tail_own<double, false>(int, const TailDesc<double>*, const TailOwner*, int,
