@@ -105,9 +105,9 @@ typedef struct chhs_problem {
  * autotune = 1 (smoother = 0, second-order scheme): chhs_init times, on the
  * problem at hand, each level's smoothing launches and keeps the fastest per
  * level (the choice then depends on the device; results agree to rounding).
- * 2D (nu1, nu2 >= 1): tiles of 256, 512 and 1024 threads (each with 16, 8 and
- * 4 rows, but on the FP32 finest level with 16; there also 64 x 32 tiles of
- * 512 and 1024 threads; the pre- and post-smoothing launches of a tile
+ * 2D (nu1, nu2 >= 1): tiles of 256, 512 and 1024 threads (on coarse levels
+ * each with 16, 8 and 4 rows; on the finest level of the default height, FP64
+ * ones of some hundred tiles also 64 x 8, FP32 ones also 64 x 32; the pre- and post-smoothing launches of a tile
  * height each take their fastest block size) and strips of 1/4, 1/2, 1, 2
  * and 4 times the default segment height.  3D: the fused step or one launch per
  * color (levels in bricks keep them).

@@ -1625,7 +1625,7 @@ int autotune3(chhs_ctx* c) {
 }
 
 // Picks, per 2D level above the tail, the fastest of: tiles with 256, 512 or
-// 1024 threads (on coarse levels each also 16, 8 and 4 rows high; on the FP32
+// 1024 threads (on coarse levels each 16, 8 and 4 rows high; on the FP32
 // finest level also 64 x 32), the pre- and the post-smoothing launches each
 // with the block size that is fastest for it, or strips with 1/4, 1/2, 1, 2 or 4
 // times the default segment height.  Runs the
@@ -1642,6 +1642,13 @@ int autotune(chhs_ctx* c) {
     }
     const chhs_opts saved = c->opts;
     c->opts.timing = 0;
+    // the finest level keeps its height by the number of tiles (FP32: 64 x 16): every
+    // candidate costs 0.7 ms of chhs_init, and of 64^2 to 2048^2 only 768^2 (576
+    // tiles) was faster with another one (64 x 8 and 1024 threads, 2030 / 2110 us for
+    // two steps), which is tried between one and four tiles per compute unit
+    const int ty0 = c->mixed ? chhs::kTileY : L.tile_y[0];
+    const bool try8 = !c->mixed && ty0 == chhs::kTileY && c->T[0].n > kWideTiles &&
+                      c->T[0].n < 4 * kWideTiles;
     if (L.both0) {
         // one kernel for every instance, the fastest: both tables are cut anew
         L.both0 = false;
@@ -1658,9 +1665,10 @@ int autotune(chhs_ctx* c) {
         };
         std::vector<Cand> cands;
         for (int ty : {chhs::kTileY, chhs::kTileYSmall, chhs::kTileYTiny}) {
-            if (l == 0 && c->mixed && ty != chhs::kTileY) continue;
+            if (l == 0 && ty != ty0) continue;
             for (int nt : {256, 512, 1024}) cands.push_back({false, nt, 0, ty});
         }
+        if (l == 0 && try8) cands.push_back({false, 1024, 0, chhs::kTileYSmall});
         // ... or, on the FP32 finest level (mixed precision), 64 x 32 (on
         // coarse FP32 levels they were never faster)
         if (l == 0 && c->mixed)
