@@ -649,7 +649,7 @@ int step3_seg(const std::vector<int>& nxs, const std::vector<int>& nys, const st
 // Bricks of one 3D level over the listed instances (extents, -1 = skip) and
 // the steps per launch, 0 for no bricks.  A finest level is in bricks if no
 // instance has more than kBrickFinest cells there and the batch at most
-// kBrickFinestAll, a coarse level if the batch has at most kBrickCoarse cells
+// kBrickAll64 (FP64) or kBrickAll32, a coarse level if the batch has at most kBrickCoarse cells
 // there: larger launches are bound by throughput, and the per-color ones, which
 // give the same bits, recompute nothing (a finest level's sums of the norm and
 // of p's mean do follow the choice, in the last bits).  Two steps while the
@@ -660,13 +660,15 @@ int step3_seg(const std::vector<int>& nxs, const std::vector<int>& nys, const st
 // its finest level per color 2675 us, in bricks 2843, 8 grids of 64^3 6187 and
 // 6588.  Mixed precision: 32^3 1571 / 1087, 48 x 32 x 64 2091 / 1420, 64^3 2615 / 1990,
 // 128^3 6836 / 6120.
-// Batches about kBrickFinestAll, the finest level per color / in bricks (with
-// coarse levels in bricks): 10 grids of 48^3 2930 / 3030 us, 14 3576 / 3856, 32 7489 /
-// 8741, 33 of 32^3 2645 / 2721, 128 8202 / 10165, 264 of 16^3 2011 / 1982, 384 2587 /
-// 2670; mixed precision, 10 of 48^3 2559 / 2842, 32 5915 / 7472, 33 of 32^3 2326 / 2455.
-constexpr long kBrickFinest = 1L << 17, kBrickFinestAll = 1L << 20, kBrickCoarse = 1L << 18;
+// Batches, the finest level per color / in bricks (one step of the scheme): 3
+// grids of 48^3 1584 / 1519 us, 4 1710 / 1719, 8 2348 / 2562, 14 3379 / 3858; of 32^3 8
+// 1193 / 1115, 12 1451 / 1453, 16 1572 / 1655, 32 2336 / 2597; of 16^3 96 1027 / 962, 128
+// 1178 / 1149, 192 1466 / 1508.  Mixed precision: of 48^3 4 1682 / 1650, 5 1864 / 1905, 14
+// 2993 / 3535; of 32^3 16 1553 / 1511, 20 1689 / 1745; of 16^3 128 1192 / 1073, 384 2292 / 2292.
+constexpr long kBrickFinest = 1L << 17, kBrickCoarse = 1L << 18;
+constexpr long kBrickAll64 = 3L << 17, kBrickAll32 = 1L << 19;
 constexpr long kBrickTwo = 256;
-int brick_tasks(std::vector<BrickTask>& out, bool finest, const std::vector<int>& nxs,
+int brick_tasks(std::vector<BrickTask>& out, bool finest, bool mixed, const std::vector<int>& nxs,
                 const std::vector<int>& nys, const std::vector<int>& nzs) {
     long total = 0;
     for (size_t i = 0; i < nxs.size(); ++i) {
@@ -675,7 +677,7 @@ int brick_tasks(std::vector<BrickTask>& out, bool finest, const std::vector<int>
         total += n;
         if (n > (finest ? kBrickFinest : kBrickCoarse)) return 0;
     }
-    if (total > (finest ? kBrickFinestAll : kBrickCoarse)) return 0;
+    if (total > (finest ? (mixed ? kBrickAll32 : kBrickAll64) : kBrickCoarse)) return 0;
     const int tx = chhs::kBrickX, ty = chhs::kBrickY, tz = chhs::kBrickZ;
     for (size_t i = 0; i < nxs.size(); ++i) {
         if (nxs[i] < 0) continue;
@@ -996,7 +998,7 @@ bool plan(const chhs_problem* p, int n_inst, const chhs_opts* o, char* base, Lay
             const int zs = mixed ? L.zseg32[l] : L.zseg64[l];
             L.z3[l] = o->smoother == 4 || zs >= kStep3MinSeg;
             if (o->smoother == 0 && !L.z3[l] && nu_pre(*o, l) > 0 && nu_post(*o, l) > 0)
-                L.brick[l] = brick_tasks(L.K[l], l == 0, lnx_t[l], lny[l], lnz[l]);
+                L.brick[l] = brick_tasks(L.K[l], l == 0, mixed, lnx_t[l], lny[l], lnz[l]);
         }
     // 3D restriction per instance (never by what else the batch holds): the
     // z-marching residual kernel on levels of at least kRes3MinCells cells, the

@@ -34,18 +34,19 @@ def test_one_vcycle_has_the_bits_of_the_per_color_launches(chhs, shape, nu, prol
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "mixed"])
-def test_batches_about_the_largest_in_bricks(chhs, precision):
-    """32 grids of 32^3 (2^20 cells) have their finest level in bricks, 33 smooth it
+@pytest.mark.parametrize("precision,most", [(0, 12), (1, 16)], ids=["fp64", "mixed"])
+def test_batches_about_the_largest_in_bricks(chhs, precision, most):
+    """`most` grids of 32^3 have their finest level in bricks, one more smooth it
     per color: the same updates, sums over the grid in another order (1e-13)."""
     import torch
     phi0 = [torch.from_numpy(uniform_field((32, 32, 32), 9750 + i, mean=0.1, amp=0.1).ravel()) for i in range(3)]
     out = []
-    for count in (32, 33):
+    for count in (most, most + 1):
         sv = chhs.Solver([chhs.make_problem((32, 32, 32), 1.0 / 32, 0.05, 2.0, 5e-4)] * count,
                          chhs.chhs_default_opts(precision=precision))
         phi = torch.cat([phi0[i % 3] for i in range(count)]).to("cuda")
         t = [phi, phi.clone(), torch.zeros_like(phi), torch.zeros_like(phi)]
+        assert (sv.level_kernels()[0][1] == 1) == (count == most)      # steps per launch
         _, st = sv.step(*t, 1)
         out.append([v[:3 * 32 ** 3] for v in t] + [[s["vcycles"] for s in st[:3]]])
     assert out[0][4] == out[1][4]
