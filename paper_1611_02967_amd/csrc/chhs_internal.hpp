@@ -373,7 +373,9 @@ template <typename T, bool CORR>
 int prepare_tail(int dim, size_t lds_bytes);
 // One workgroup per listed instance: the V-cycle over levels info.tail ..
 // info.nlev - 1 of that instance; bit l of cur_mask = current copy of u on
-// level l.
+// level l.  res, cycles (FP64; res null: not): where the tail holds the finest
+// level, a step's first cycle (cycles[inst] = 0) takes out the mean of p in res
+// slot 4.
 template <typename T, bool CORR>
 void launch_tail(int dim, const LevelDesc<T>* desc, const InstInfo* info, const int* insts,
                  int ninst, const int* active, unsigned cur_mask, const CycleShape& shape,
