@@ -107,9 +107,9 @@ typedef struct chhs_problem {
  * level (the choice then depends on the device; results agree to rounding).
  * 2D (nu1, nu2 >= 1): tiles of 256, 512 and 1024 threads (on coarse levels
  * each with 16, 8 and 4 rows; on the finest level of the default height, FP64
- * ones of some hundred tiles also 64 x 8, FP32 ones also 64 x 32; the pre- and post-smoothing launches of a tile
- * height each take their fastest block size) and strips of 1/4, 1/2, 1, 2
- * and 4 times the default segment height.  3D: the fused step or one launch per
+ * ones of some hundred tiles also 64 x 8, FP32 ones also 64 x 32; the pre- and
+ * post-smoothing launches of a tile height each take their fastest block size)
+ * and strips of 1/4, 1/2, 1, 2 and 4 times the default segment height.  3D: the fused step or one launch per
  * color (levels in bricks keep them).
  * order = 2 (default; 0 means the same) solves the second-order scheme
  * (2.4)-(2.7).  order = 1 solves instead the first-order convex-splitting step

@@ -3,9 +3,9 @@
 // Owns the multigrid hierarchies of a batch of independent instances carved
 // out of the caller's workspace, the task tables that let one launch per level
 // cover every instance, the FAS V-cycle schedule (optionally replayed as a
-// captured HIP graph), the per-instance stopping test (a small pinned
-// mirror that each cycle's reduction writes), the mixed-precision iterative refinement, and the time-step loop
-// with its state rotation.
+// captured HIP graph), the per-instance stopping test (on a small pinned mirror
+// that each cycle's reduction writes), the mixed-precision iterative refinement,
+// and the time-step loop with its state rotation.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -649,12 +649,12 @@ int step3_seg(const std::vector<int>& nxs, const std::vector<int>& nys, const st
 // Bricks of one 3D level over the listed instances (extents, -1 = skip) and
 // the steps per launch, 0 for no bricks.  A finest level is in bricks if no
 // instance has more than kBrickFinest cells there and the batch at most
-// kBrickAll64 (FP64) or kBrickAll32, a coarse level if the batch has at most kBrickCoarse cells
-// there: larger launches are bound by throughput, and the per-color ones, which
-// give the same bits, recompute nothing (a finest level's sums of the norm and
-// of p's mean do follow the choice, in the last bits).  Two steps while the
-// bricks of two steps (one workgroup per compute unit, by their LDS) are all
-// resident at once.  Two steps of the scheme, per-color launches / bricks: 16^3
+// kBrickAll64 (FP64) or kBrickAll32 (mixed precision), a coarse level if the batch
+// has at most kBrickCoarse cells there: larger launches are bound by throughput,
+// and the per-color ones, which give the same bits, recompute nothing (a finest
+// level's sums of the norm and of p's mean do follow the choice, in the last
+// bits).  Two steps while the bricks of two steps (one workgroup per compute
+// unit, by their LDS) are all resident at once.  Two steps of the scheme, per-color launches / bricks: 16^3
 // 971 / 631 us, 32^3 1565 / 949, 48 x 32 x 64 2100 / 1300, the coarse levels of 64^3
 // 2583 / 2040 and of 128^3 7670 / 7035, 64 grids of 16^3 1582 / 1358; beyond: 80^3 with
 // its finest level per color 2675 us, in bricks 2843, 8 grids of 64^3 6187 and
